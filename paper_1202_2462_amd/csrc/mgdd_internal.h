@@ -84,7 +84,9 @@ struct Level1 {  // coarse level of the current P
     void *Dh32 = nullptr;
     int *cnbr = nullptr;                    // [Vc][9] coarse neighbour (self first)
     int *corder = nullptr;                  // [Vc] order in which the coarse step visits the coarse sites
-    int *agg_sites = nullptr;               // [Vc][Va] device site of each local site of an aggregate
+    int *agg_sites = nullptr;               // [Vc][Va] device sites of each aggregate, ascending
+    // for each direction mu the sites on the + face of each aggregate, [Vc][Va / agg_mu], one direction after the other
+    int *face_sites = nullptr;
     int *site_agg = nullptr;                // [V] aggregate of each device site
     void *tv64 = nullptr;                   // the N test vectors P was built from
 };

@@ -264,395 +264,6 @@ __global__ __launch_bounds__(TPB) void prolong_kernel(int V, int Vc, int N, cons
     for (int c = 0; c < 12; c++) fr[(size_t)c * V + d] = mk<SF>((SF)acc[c].x, (SF)acc[c].y);
 }
 
-// ---------------------------------------------------------------- terms of D for one column of D_c
-//
-// For the prolonged unit vector P_j (test vector k restricted to chirality
-// chi), W_0 = A P_j - 1/2 (hops that stay inside the aggregate) and, for each
-// face direction dd = 1 + 2 mu (+mu) or 2 + 2 mu (-mu), W_dd = the single hop of
-// D that leaves the aggregate through that face (zero elsewhere). Written as 9
-// fine fields [dd][12][V].
-template <int MU, bool FWD>
-__device__ inline void face_term(const LinkViews<double> &U, const FieldView<double> &pj, int chi, int d, int dn,
-                                 bool crosses, double2 *self, double2 *Wdir, size_t V) {
-    double2 psi[12], u[9], t[12];
-    load_spinor<double>(pj, dn, psi);
-#pragma unroll
-    for (int c = 0; c < 12; c++) {
-        if ((c >= 6) != (chi != 0)) psi[c] = make_double2(0, 0);
-        t[c] = make_double2(0, 0);
-    }
-    load_link<double, MU>(U, FWD ? d : dn, u);
-    hop<double, MU, FWD>(t, u, psi);
-    FieldView<double> w(Wdir, V, 12);
-#pragma unroll
-    for (int c = 0; c < 12; c++) {
-        if (crosses) {
-            w.st(c, d, cscale(t[c], -0.5));
-        } else {
-            self[c] = cadd(self[c], t[c]);
-            w.st(c, d, make_double2(0, 0));
-        }
-    }
-}
-
-__global__ __launch_bounds__(TPB) void dc_terms_kernel(Geom g, AggGeom ag, const double2 *__restrict__ Up,
-                                                       const double2 *__restrict__ Ap, const double2 *__restrict__ Pk,
-                                                       int chi, double2 *__restrict__ W) {
-    const int d = blockIdx.x * TPB + threadIdx.x;
-    if (d >= g.V) return;
-    const size_t V = g.V;
-    int X[4], nbr[8];
-    site_coords(g, d, X);
-    site_neighbours(g, d, nbr);
-    LinkViews<double> U(Up, V);
-    CloverViews<double> A(Ap, V);
-    FieldView<double> pj(Pk, V, 12);
-    double2 self[12], psi[12], ap[12];
-#pragma unroll
-    for (int c = 0; c < 12; c++) self[c] = make_double2(0, 0);
-    bool last[4], first[4];
-#pragma unroll
-    for (int m = 0; m < 4; m++) {
-        int r = X[m] % ag.a[m];
-        last[m] = r == ag.a[m] - 1;   // the +m hop leaves the aggregate
-        first[m] = r == 0;            // the -m hop leaves the aggregate
-    }
-    const size_t fs = (size_t)12 * V;
-    face_term<0, true>(U, pj, chi, d, nbr[0], last[0], self, W + 1 * fs, V);
-    face_term<0, false>(U, pj, chi, d, nbr[1], first[0], self, W + 2 * fs, V);
-    face_term<1, true>(U, pj, chi, d, nbr[2], last[1], self, W + 3 * fs, V);
-    face_term<1, false>(U, pj, chi, d, nbr[3], first[1], self, W + 4 * fs, V);
-    face_term<2, true>(U, pj, chi, d, nbr[4], last[2], self, W + 5 * fs, V);
-    face_term<2, false>(U, pj, chi, d, nbr[5], first[2], self, W + 6 * fs, V);
-    face_term<3, true>(U, pj, chi, d, nbr[6], last[3], self, W + 7 * fs, V);
-    face_term<3, false>(U, pj, chi, d, nbr[7], first[3], self, W + 8 * fs, V);
-    // self term: A P_j - 1/2 (hops that stay inside the aggregate)
-    load_spinor<double>(pj, d, psi);
-#pragma unroll
-    for (int c = 0; c < 12; c++) if ((c >= 6) != (chi != 0)) psi[c] = make_double2(0, 0);
-    clover_mv<double>(A, d, psi, ap);
-    FieldView<double> w0(W, V, 12);
-#pragma unroll
-    for (int c = 0; c < 12; c++) w0.st(c, d, csub(ap[c], cscale(self[c], 0.5)));
-}
-
-// Fallback for aggregates with an extent of 1 in some direction (a site then
-// lies on both faces of that direction): one workgroup per (aggregate a,
-// column j = (chi', k')), one thread per site x of a: the thread forms the 9
-// terms of D applied to the prolonged unit vector P e_j at x (self term:
-// clover plus the hops that stay in a; one face term per direction, nonzero
-// on that face only), then projects all 9 on every P_k(x) of both
-// chiralities in one pass over P. Block layout [a][dir][col][row].
-template <int MU, bool FWD>
-__device__ inline void term_hop(const LinkViews<double> &U, const FieldView<double> &pj, int chi, int d, int dn,
-                                double2 *acc) {
-    double2 psi[12], u[9];
-    load_spinor<double>(pj, dn, psi);
-#pragma unroll
-    for (int c = 0; c < 12; c++)
-        if ((c >= 6) != (chi != 0)) psi[c] = make_double2(0, 0);
-    load_link<double, MU>(U, FWD ? d : dn, u);
-    hop<double, MU, FWD>(acc, u, psi);
-}
-
-// the hop of one direction: into the face term when it leaves the aggregate
-// (scaled by -1/2), else added to the self sum
-template <int MU, bool FWD>
-__device__ inline void term_into(const LinkViews<double> &U, const FieldView<double> &pj, int chi, int d, int dn,
-                                 bool crosses, double2 *self, double2 *face) {
-    double2 t[12];
-#pragma unroll
-    for (int c = 0; c < 12; c++) t[c] = make_double2(0, 0);
-    term_hop<MU, FWD>(U, pj, chi, d, dn, t);
-#pragma unroll
-    for (int c = 0; c < 12; c++) {
-        face[c] = crosses ? cscale(t[c], -0.5) : make_double2(0, 0);
-        self[c] = crosses ? self[c] : cadd(self[c], t[c]);
-    }
-}
-
-__global__ __launch_bounds__(256) void dc_build_thin_kernel(Geom g, AggGeom ag, int N, int Va, const int *__restrict__ agg_sites,
-                                                       const double2 *__restrict__ Up, const double2 *__restrict__ Ap,
-                                                       const double2 *__restrict__ P, double2 *__restrict__ Dc,
-                                                       int nwg) {
-    extern __shared__ double dred[];  // reduction space (see below)
-    const int n2 = 2 * N;
-    const int w = xcd_block(nwg);
-    const int a = w / n2, j = w % n2, chi = j / N, kk = j % N;
-    const size_t V = g.V;
-    const int l = threadIdx.x;
-    const bool active = l < Va;
-    double2 wt[9][12];
-#pragma unroll
-    for (int t = 0; t < 9; t++)
-#pragma unroll
-        for (int c = 0; c < 12; c++) wt[t][c] = make_double2(0, 0);
-    int d = 0;
-    if (active) {
-        d = agg_sites[(size_t)a * Va + l];
-        int X[4], nbr[8];
-        site_coords(g, d, X);
-        site_neighbours(g, d, nbr);
-        LinkViews<double> U(Up, V);
-        CloverViews<double> A(Ap, V);
-        FieldView<double> pj(P + (size_t)kk * 12 * V, V, 12);
-        double2 self[12];
-#pragma unroll
-        for (int c = 0; c < 12; c++) self[c] = make_double2(0, 0);
-        bool last[4], first[4];
-#pragma unroll
-        for (int m = 0; m < 4; m++) {
-            int r = X[m] % ag.a[m];
-            last[m] = r == ag.a[m] - 1;   // the +m hop leaves the aggregate
-            first[m] = r == 0;            // the -m hop leaves the aggregate
-        }
-        term_into<0, true>(U, pj, chi, d, nbr[0], last[0], self, wt[1]);
-        term_into<0, false>(U, pj, chi, d, nbr[1], first[0], self, wt[2]);
-        term_into<1, true>(U, pj, chi, d, nbr[2], last[1], self, wt[3]);
-        term_into<1, false>(U, pj, chi, d, nbr[3], first[1], self, wt[4]);
-        term_into<2, true>(U, pj, chi, d, nbr[4], last[2], self, wt[5]);
-        term_into<2, false>(U, pj, chi, d, nbr[5], first[2], self, wt[6]);
-        term_into<3, true>(U, pj, chi, d, nbr[6], last[3], self, wt[7]);
-        term_into<3, false>(U, pj, chi, d, nbr[7], first[3], self, wt[8]);
-        double2 psi[12], ap[12];
-        load_spinor<double>(pj, d, psi);
-#pragma unroll
-        for (int c = 0; c < 12; c++)
-            if ((c >= 6) != (chi != 0)) psi[c] = make_double2(0, 0);
-        clover_mv<double>(A, d, psi, ap);
-#pragma unroll
-        for (int c = 0; c < 12; c++) wt[0][c] = csub(ap[c], cscale(self[c], 0.5));
-    }
-    // projections onto the N test-vector columns of aggregate a: for each k
-    // every thread writes its 36 partial products (9 terms x re/im x two row
-    // chiralities) to LDS, then S threads per product add the partials in a
-    // fixed order (a tree through LDS costs fewer instructions than 36
-    // cross-lane reductions per wave)
-    const int nthr = blockDim.x, S = nthr / 36 > 0 ? nthr / 36 : 1;
-    double *red = dred;                         // [36][nthr]
-    double *p2 = red + 36 * nthr;               // [36][S]
-    double *res = p2 + 36 * S;                  // [N][36]
-    for (int k = 0; k < N; k++) {
-        double2 pk[12];
-        if (active) {
-            FieldView<double> fk(P + (size_t)k * 12 * V, V, 12);
-            load_spinor<double>(fk, d, pk);
-        } else {
-#pragma unroll
-            for (int c = 0; c < 12; c++) pk[c] = make_double2(0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < 9; t++) {
-            double p[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int c = 0; c < 12; c++) {
-                double re = pk[c].x * wt[t][c].x + pk[c].y * wt[t][c].y;
-                double im = pk[c].x * wt[t][c].y - pk[c].y * wt[t][c].x;
-                p[c < 6 ? 0 : 2] += re;
-                p[c < 6 ? 1 : 3] += im;
-            }
-#pragma unroll
-            for (int q = 0; q < 4; q++) red[(t * 4 + q) * nthr + threadIdx.x] = p[q];
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < 36 * S) {
-            const int q = threadIdx.x / S, sidx = threadIdx.x % S;
-            double acc = 0;
-            for (int i = sidx; i < nthr; i += S) acc += red[q * nthr + i];
-            p2[q * S + sidx] = acc;
-        }
-        __syncthreads();
-        if (threadIdx.x < 36) {
-            double acc = 0;
-            for (int sidx = 0; sidx < S; sidx++) acc += p2[threadIdx.x * S + sidx];
-            res[k * 36 + threadIdx.x] = acc;
-        }
-    }
-    __syncthreads();
-    const size_t blk = (size_t)n2 * n2;
-    for (int e = threadIdx.x; e < 9 * n2; e += blockDim.x) {
-        int t = e / n2, i = e % n2;
-        int rchi = i / N, k = i % N;
-        const double *o = res + (size_t)k * 36 + t * 4;
-        Dc[((size_t)a * 9 + t) * blk + (size_t)j * n2 + i] = make_double2(o[2 * rchi], o[2 * rchi + 1]);
-    }
-}
-
-// D_c for aggregates of at most 256 sites with every extent >= 2: one
-// workgroup per (aggregate a, column j = (chi', k'), row chirality h), one
-// thread per site x of a. With extents >= 2 a site lies on at most one face
-// per direction, so the thread keeps five 6-component terms: the h half of
-// the self term (clover block h on P_j, which is zero unless h = chi', minus
-// 1/2 the hops that stay in a) and, per direction mu, the h half of -1/2 the
-// hop that leaves a through the face the site lies on (zero inside). For
-// each k the products with the h half of P_k(x) give 10 partial sums per
-// thread; each wave spreads them into its 18 sums (self, + face and - face of
-// each direction, re and im) through a wave-private LDS tile, read back by 54
-// lanes in three fixed row ranges, so the k loop has no workgroup barrier.
-// The per-wave sums are added in wave order at the end.
-constexpr int DCB_COLS = 18;   // per-wave sums for one k
-constexpr int DCB_LD = 65;     // tile row length in doubles (64 lanes + 1: no bank conflicts)
-
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// one hop of D on P_j (test vector restricted to chirality chi), all 12
-// components, without the factor -1/2
-template <int MU, bool FWD>
-__device__ inline void col_hop(const LinkViews<double> &U, const FieldView<double> &pj, int chi, int d, int dn,
-                               double2 *t) {
-    double2 psi[12], u[9];
-#pragma unroll
-    for (int c = 0; c < 12; c++) {
-        t[c] = make_double2(0, 0);
-        psi[c] = ((c >= 6) == (chi != 0)) ? pj.ld(c, dn) : make_double2(0, 0);
-    }
-    load_link<double, MU>(U, FWD ? d : dn, u);
-    hop<double, MU, FWD>(t, u, psi);
-}
-
-// both hops of direction MU: the one that leaves the aggregate (at most one
-// when the extent is >= 2) into face, the others into self (h halves)
-template <int MU>
-__device__ inline void col_dir(const LinkViews<double> &U, const FieldView<double> &pj, int chi, int h, int d,
-                               const int *nbr, bool last, bool first, double2 *self, double2 *face) {
-    double2 t[12];
-    col_hop<MU, true>(U, pj, chi, d, nbr[2 * MU], t);
-#pragma unroll
-    for (int c = 0; c < 6; c++) {
-        const double2 v = h ? t[6 + c] : t[c];
-        if (last) face[c] = cscale(v, -0.5);
-        else self[c] = cadd(self[c], v);
-    }
-    col_hop<MU, false>(U, pj, chi, d, nbr[2 * MU + 1], t);
-#pragma unroll
-    for (int c = 0; c < 6; c++) {
-        const double2 v = h ? t[6 + c] : t[c];
-        if (first) face[c] = cscale(v, -0.5);
-        else self[c] = cadd(self[c], v);
-    }
-}
-
-__global__ __launch_bounds__(256) void dc_build_kernel(Geom g, AggGeom ag, int N, int Va, const int *__restrict__ agg_sites,
-                                                       const double2 *__restrict__ Up, const double2 *__restrict__ Ap,
-                                                       const double2 *__restrict__ P, double2 *__restrict__ Dc,
-                                                       int nwg) {
-    extern __shared__ double dsm[];
-    const int n2 = 2 * N;
-    const int w = xcd_block(nwg);
-    const int h = w & 1, j = (w >> 1) % n2, a = (w >> 1) / n2, chi = j / N, kk = j % N;
-    const size_t V = g.V;
-    const int l = threadIdx.x, lane = l & 63, wave = l >> 6, nw = blockDim.x >> 6;
-    const bool active = l < Va;
-    double2 wt[5][6];
-#pragma unroll
-    for (int s = 0; s < 5; s++)
-#pragma unroll
-        for (int c = 0; c < 6; c++) wt[s][c] = make_double2(0, 0);
-    bool last[4] = {false, false, false, false}, first[4] = {false, false, false, false};
-    int d = 0;
-    if (active) {
-        d = agg_sites[(size_t)a * Va + l];
-        int X[4], nbr[8];
-        site_coords(g, d, X);
-        site_neighbours(g, d, nbr);
-        LinkViews<double> U(Up, V);
-        FieldView<double> pj(P + (size_t)kk * 12 * V, V, 12);
-#pragma unroll
-        for (int m = 0; m < 4; m++) {
-            const int r = X[m] % ag.a[m];
-            last[m] = r == ag.a[m] - 1;   // the +m hop leaves the aggregate
-            first[m] = r == 0;            // the -m hop leaves the aggregate
-        }
-        double2 self[6];
-#pragma unroll
-        for (int c = 0; c < 6; c++) self[c] = make_double2(0, 0);
-        col_dir<0>(U, pj, chi, h, d, nbr, last[0], first[0], self, wt[1]);
-        col_dir<1>(U, pj, chi, h, d, nbr, last[1], first[1], self, wt[2]);
-        col_dir<2>(U, pj, chi, h, d, nbr, last[2], first[2], self, wt[3]);
-        col_dir<3>(U, pj, chi, h, d, nbr, last[3], first[3], self, wt[4]);
-        double2 ap[6];
-#pragma unroll
-        for (int c = 0; c < 6; c++) ap[c] = make_double2(0, 0);
-        if (h == chi) {   // the clover term is block diagonal in chirality
-            FieldView<double> ab(Ap + (size_t)h * 18 * V, V, 18);   // packed block h
-            double2 pa[18], in[6];
-#pragma unroll
-            for (int q = 0; q < 18; q++) pa[q] = ab.ld(q, d);
-#pragma unroll
-            for (int c = 0; c < 6; c++) in[c] = pj.ld(6 * h + c, d);
-            herm6_mv<double>(pa, in, ap);
-        }
-#pragma unroll
-        for (int c = 0; c < 6; c++) wt[0][c] = csub(ap[c], cscale(self[c], 0.5));
-    }
-    double *tile = dsm + (size_t)wave * DCB_COLS * DCB_LD;   // [18][65], this wave only
-    double *outw = dsm + (size_t)nw * DCB_COLS * DCB_LD;     // [N][nw][18]
-    const int col = lane % DCB_COLS, part = lane / DCB_COLS, r0 = 22 * part;
-    double2 pk[6];
-    {
-        FieldView<double> f0(P, V, 12);
-#pragma unroll
-        for (int c = 0; c < 6; c++) pk[c] = active ? f0.ld(6 * h + c, d) : make_double2(0, 0);
-    }
-    for (int k = 0; k < N; k++) {
-        double2 pn[6];
-        const bool more = active && k + 1 < N;
-        FieldView<double> fn(P + (size_t)(more ? k + 1 : k) * 12 * V, V, 12);
-#pragma unroll
-        for (int c = 0; c < 6; c++) pn[c] = more ? fn.ld(6 * h + c, d) : make_double2(0, 0);
-        double s[5][2];
-#pragma unroll
-        for (int q = 0; q < 5; q++) {
-            double re = 0, im = 0;
-#pragma unroll
-            for (int c = 0; c < 6; c++) {
-                re += pk[c].x * wt[q][c].x + pk[c].y * wt[q][c].y;
-                im += pk[c].x * wt[q][c].y - pk[c].y * wt[q][c].x;
-            }
-            s[q][0] = re;
-            s[q][1] = im;
-        }
-        tile[0 * DCB_LD + lane] = s[0][0];
-        tile[1 * DCB_LD + lane] = s[0][1];
-#pragma unroll
-        for (int m = 0; m < 4; m++) {
-            tile[(2 + 4 * m) * DCB_LD + lane] = last[m] ? s[1 + m][0] : 0.0;
-            tile[(3 + 4 * m) * DCB_LD + lane] = last[m] ? s[1 + m][1] : 0.0;
-            tile[(4 + 4 * m) * DCB_LD + lane] = first[m] ? s[1 + m][0] : 0.0;
-            tile[(5 + 4 * m) * DCB_LD + lane] = first[m] ? s[1 + m][1] : 0.0;
-        }
-        wave_sync();
-        double acc = 0;
-        if (lane < 3 * DCB_COLS) {
-#pragma unroll
-            for (int q = 0; q < 22; q++)
-                if (r0 + q < 64) acc += tile[col * DCB_LD + r0 + q];
-        }
-        const double a1 = __shfl(acc, lane + DCB_COLS, 64), a2 = __shfl(acc, lane + 2 * DCB_COLS, 64);
-        if (lane < DCB_COLS) outw[((size_t)k * nw + wave) * DCB_COLS + lane] = (acc + a1) + a2;
-        wave_sync();
-#pragma unroll
-        for (int c = 0; c < 6; c++) pk[c] = pn[c];
-    }
-    __syncthreads();
-    const size_t blk = (size_t)n2 * n2;
-    for (int e = threadIdx.x; e < 9 * N; e += blockDim.x) {
-        const int t = e / N, k = e % N;
-        const int c0 = t == 0 ? 0 : 2 + 2 * (t - 1);   // + face of mu: 2 + 4 mu, - face: 4 + 4 mu
-        double re = 0, im = 0;
-        for (int q = 0; q < nw; q++) {
-            const double *o = outw + ((size_t)k * nw + q) * DCB_COLS + c0;
-            re += o[0];
-            im += o[1];
-        }
-        Dc[((size_t)a * 9 + t) * blk + (size_t)j * n2 + (size_t)h * N + k] = make_double2(re, im);
-    }
-}
-
 // ---------------------------------------------------------------- coarse stencil y = D_c x
 //
 // One workgroup of 1024 threads per (coarse site, right-hand side): the 9 2N
@@ -756,38 +367,6 @@ __global__ __launch_bounds__(64) void coarse_apply_mfma_kernel(int Vc, int N, in
     }
 }
 
-template <typename T>
-__global__ void dc_to_f32(int Vc, int n2, const double2 *__restrict__ src, C<T> *__restrict__ dst) {
-    size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t n = (size_t)Vc * 9 * n2 * n2;
-    if (e < n) dst[e] = mk<T>((T)src[e].x, (T)src[e].y);
-}
-
-// FP32 copy of the self block and the four forward-hop blocks of every
-// coarse site, [Vc][5][col][row] (block q: direction 0 for q = 0, the +mu hop
-// 1 + 2 mu for q = 1 + mu)
-__global__ void dc_compact_f32(int Vc, int n2, const double2 *__restrict__ src, float2 *__restrict__ dst) {
-    const size_t blk = (size_t)n2 * n2;
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (size_t)Vc * 5 * blk) return;
-    const size_t a = e / (5 * blk), r = e % (5 * blk);
-    const int q = (int)(r / blk);
-    const int t = q == 0 ? 0 : 2 * q - 1;
-    const double2 v = src[(a * 9 + t) * blk + r % blk];
-    dst[e] = make_float2((float)v.x, (float)v.y);
-}
-
-static int coarse_to_f32(Ctx *c) {
-    Level1 &L1 = c->c;
-    const int n2 = 2 * L1.N;
-    const size_t blk = (size_t)n2 * n2, n = (size_t)L1.Vc * 9 * blk, nh = (size_t)L1.Vc * 5 * blk;
-    dc_to_f32<float><<<(unsigned)((n + 255) / 256), 256, 0, c->stream>>>(L1.Vc, n2, (const double2 *)L1.Dc64,
-                                                                        (float2 *)L1.Dc32);
-    dc_compact_f32<<<(unsigned)((nh + 255) / 256), 256, 0, c->stream>>>(L1.Vc, n2, (const double2 *)L1.Dc64,
-                                                                      (float2 *)L1.Dh32);
-    return hip_check(c, hipGetLastError(), "D_c convert");
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------- host side
@@ -849,12 +428,20 @@ int transfer_setup(Ctx *c, const int *agg, int N) {
     // free the previous level (and the third level built on it)
     level2_free(c);
     void *old[] = {L1.P64, L1.P32, L1.P16, L1.Dc64, L1.Dc32, L1.Dh32, L1.cnbr, L1.corder, L1.agg_sites, L1.site_agg,
-                   L1.tv64};
+                   L1.face_sites, L1.tv64};
     (void)hipStreamSynchronize(c->stream);
     for (void *p : old) dfree(c, p);
     L1 = Level1();
-    // tables: fine sites of each aggregate (local lexicographic order), aggregate of each site
-    std::vector<int> agg_sites((size_t)Vc * Va), site_agg(g.V), cnbr((size_t)Vc * 9);
+    // tables: fine sites of each aggregate in ascending device order (so that
+    // consecutive entries are neighbours in memory as far as the aggregate
+    // allows), those of them on its + face in each direction, the aggregate
+    // of each site
+    std::vector<int> agg_sites((size_t)Vc * Va), site_agg(g.V), cnbr((size_t)Vc * 9), nsite(Vc, 0);
+    std::vector<int> face[4], nface[4];
+    for (int m = 0; m < 4; m++) {
+        face[m].resize((size_t)Vc * (Va / agg[m]));
+        nface[m].assign(Vc, 0);
+    }
     std::vector<uint32_t> coord;
     std::vector<int> bn, lp;
     Geom hg{};
@@ -863,22 +450,19 @@ int transfer_setup(Ctx *c, const int *agg, int N) {
     hg.blk_coord = coord.data();
     hg.blk_nbr = bn.data();
     hg.pos_of_lex = lp.data();
-    std::vector<int> dev_of_lex(g.V);
-    for (int d = 0; d < g.V; d++) dev_of_lex[lex_of(hg, d)] = d;
+    for (int d = 0; d < g.V; d++) {
+        int X[4], ac[4];
+        site_coords(hg, d, X);
+        for (int m = 0; m < 4; m++) ac[m] = X[m] / agg[m];
+        const int a = ac[0] + Lc[0] * (ac[1] + Lc[1] * (ac[2] + Lc[2] * ac[3]));
+        agg_sites[(size_t)a * Va + nsite[a]++] = d;
+        site_agg[d] = a;
+        for (int m = 0; m < 4; m++)
+            if (X[m] == ac[m] * agg[m] + agg[m] - 1) face[m][(size_t)a * (Va / agg[m]) + nface[m][a]++] = d;
+    }
     for (int a = 0; a < Vc; a++) {
         int t = a, ac[4];
         for (int m = 0; m < 4; m++) { ac[m] = t % Lc[m]; t /= Lc[m]; }
-        int l = 0;
-        for (int x3 = 0; x3 < agg[3]; x3++)
-            for (int x2 = 0; x2 < agg[2]; x2++)
-                for (int x1 = 0; x1 < agg[1]; x1++)
-                    for (int x0 = 0; x0 < agg[0]; x0++) {
-                        int X[4] = {ac[0] * agg[0] + x0, ac[1] * agg[1] + x1, ac[2] * agg[2] + x2, ac[3] * agg[3] + x3};
-                        int s = X[0] + g.L[0] * (X[1] + g.L[1] * (X[2] + g.L[2] * X[3]));
-                        int d = dev_of_lex[s];
-                        agg_sites[(size_t)a * Va + l++] = d;
-                        site_agg[d] = a;
-                    }
         cnbr[(size_t)a * 9] = a;
         for (int m = 0; m < 4; m++)
             for (int dir = 0; dir < 2; dir++) {
@@ -901,12 +485,16 @@ int transfer_setup(Ctx *c, const int *agg, int N) {
     L1.corder = (int *)dalloc(c, corder.size() * sizeof(int));
     L1.agg_sites = (int *)dalloc(c, agg_sites.size() * sizeof(int));
     L1.site_agg = (int *)dalloc(c, site_agg.size() * sizeof(int));
+    std::vector<int> faces;
+    for (int m = 0; m < 4; m++) faces.insert(faces.end(), face[m].begin(), face[m].end());
+    L1.face_sites = (int *)dalloc(c, faces.size() * sizeof(int));
     if (!L1.P64 || !L1.tv64 || !L1.P32 || !L1.P16 || !L1.Dc64 || !L1.Dc32 || !L1.Dh32 || !L1.cnbr || !L1.corder ||
-        !L1.agg_sites || !L1.site_agg)
+        !L1.agg_sites || !L1.site_agg || !L1.face_sites)
         return MGDD_ENOMEM;
     int rc = hip_check(c, hipMemcpy(L1.cnbr, cnbr.data(), cnbr.size() * sizeof(int), hipMemcpyHostToDevice), "copy");
     if (!rc) rc = hip_check(c, hipMemcpy(L1.corder, corder.data(), corder.size() * sizeof(int), hipMemcpyHostToDevice), "copy");
     if (!rc) rc = hip_check(c, hipMemcpy(L1.agg_sites, agg_sites.data(), agg_sites.size() * sizeof(int), hipMemcpyHostToDevice), "copy");
+    if (!rc) rc = hip_check(c, hipMemcpy(L1.face_sites, faces.data(), faces.size() * sizeof(int), hipMemcpyHostToDevice), "copy");
     if (!rc) rc = hip_check(c, hipMemcpy(L1.site_agg, site_agg.data(), site_agg.size() * sizeof(int), hipMemcpyHostToDevice), "copy");
     if (rc) return rc;
     for (int m = 0; m < 4; m++) { L1.agg[m] = agg[m]; L1.Lc[m] = Lc[m]; }
@@ -990,57 +578,6 @@ int launch_prolong(Ctx *c, int prec, int nrhs, const void *coarse, void *fine) {
         prolong_kernel<float, _Float16, _Float16><<<nwg, TPB, 0, c->stream>>>(
             c->g.V, L1.Vc, L1.N, L1.site_agg, (const half_cx *)L1.P16, (const float2 *)coarse, (half_cx *)fine, nrhs);
     return hip_check(c, hipGetLastError(), "prolong kernel");
-}
-
-int launch_coarse_build(Ctx *c) {
-    Level1 &L1 = c->c;
-    const Geom &g = c->g;
-    const int N = L1.N, n2 = 2 * N;
-    bool thin = false;
-    for (int m = 0; m < 4; m++) thin = thin || L1.agg[m] < 2;
-    if (L1.Va <= 256) {
-        AggGeom ag{};
-        for (int m = 0; m < 4; m++) ag.a[m] = L1.agg[m];
-        int threads = ((L1.Va + 63) / 64) * 64;
-        if (!thin) {
-            const int nwg = L1.Vc * n2 * 2;
-            const size_t lds = ((size_t)(threads / 64) * DCB_COLS * DCB_LD + (size_t)N * (threads / 64) * DCB_COLS) *
-                               sizeof(double);
-            dc_build_kernel<<<nwg, threads, lds, c->stream>>>(g, ag, N, L1.Va, L1.agg_sites, (const double2 *)c->U64,
-                                                               (const double2 *)c->A64, (const double2 *)L1.P64,
-                                                               (double2 *)L1.Dc64, nwg);
-        } else {
-            const int nwg = L1.Vc * n2;
-            const int S = threads / 36 > 0 ? threads / 36 : 1;
-            size_t lds = ((size_t)36 * threads + 36 * S + (size_t)36 * N) * sizeof(double);
-            dc_build_thin_kernel<<<nwg, threads, lds, c->stream>>>(g, ag, N, L1.Va, L1.agg_sites,
-                                                                    (const double2 *)c->U64, (const double2 *)c->A64,
-                                                                    (const double2 *)L1.P64, (double2 *)L1.Dc64, nwg);
-        }
-        int rc = hip_check(c, hipGetLastError(), "D_c build kernel");
-        if (rc) return rc;
-        return coarse_to_f32(c);
-    }
-    // aggregates of more than 256 sites: terms of each column as 9 fine
-    // fields, then a restriction of those fields
-    double2 *W = (double2 *)ensure_scratch(c, (size_t)9 * 12 * g.V * 16);
-    if (!W) return MGDD_ENOMEM;
-    AggGeom ag{};
-    for (int m = 0; m < 4; m++) ag.a[m] = L1.agg[m];
-    unsigned nwg = (unsigned)((g.V + TPB - 1) / TPB);
-    const size_t blk = (size_t)n2 * n2;
-    for (int chi = 0; chi < 2; chi++)
-        for (int k = 0; k < N; k++) {
-            int j = chi * N + k;
-            dc_terms_kernel<<<nwg, TPB, 0, c->stream>>>(g, ag, (const double2 *)c->U64, (const double2 *)c->A64,
-                                                       (const double2 *)L1.P64 + (size_t)k * 12 * g.V, chi, W);
-            int rc = hip_check(c, hipGetLastError(), "D_c terms kernel");
-            if (rc) return rc;
-            // column j of the 9 blocks of every coarse site: out[a][dd][j][row]
-            rc = launch_restrict_ex(c, MGDD_F64, 9, L1.P64, W, (double2 *)L1.Dc64 + (size_t)j * n2, 9 * blk, blk);
-            if (rc) return rc;
-        }
-    return coarse_to_f32(c);
 }
 
 int launch_stencil_apply(Ctx *c, const StencilOp &op, int prec, int nrhs, const void *in, void *out) {
