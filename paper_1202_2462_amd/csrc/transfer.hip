@@ -4,6 +4,7 @@
 // column from the terms of D (self term plus the hops that cross each face of
 // an aggregate) followed by a restriction. The coarse stencil apply lives here
 // as well.
+#include "lanes.h"
 #include "stencil.h"
 #include "transfer.h"
 #include "coarse.h"
@@ -93,76 +94,110 @@ __global__ __launch_bounds__(TPB) void build_P_kernel(int V, int Va, int N, cons
 }
 
 // The same orthonormalisation for aggregates of at most TPB sites, one thread
-// per site holding the 6 components of the column being orthonormalised in
-// registers: each step loads one earlier column once, and each sum over the
-// block takes one barrier (two alternating LDS slots). Per-thread sums, the
-// butterfly and the order over waves are those of build_P_kernel.
-__device__ inline double2 block_sum2_1(double a, double b, double *red) {
-    a = wsum(a);
-    b = wsum(b);
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if ((threadIdx.x & 63) == 0) { red[2 * w] = a; red[2 * w + 1] = b; }
+// per site and PANEL columns at a time in registers (6 components each): an
+// earlier column is loaded once per panel and its products with the PANEL
+// columns are summed over the workgroup together (one barrier, two alternating
+// LDS slots); within the panel a column's norm and its products with the
+// later ones are. Each column still has the earlier ones taken off one after
+// the other, so this is modified Gram-Schmidt in column order.
+// Bound: the reads of the earlier columns (from the Infinity Cache: 256
+// workgroups' columns do not fit L2) and the latency of the sums. 24^3 x 48
+// lattice, 3x4x4x4 aggregates, N = 21: 4.3 ms; one column at a time read
+// every earlier column N times over (60 GB) and took 10.8 ms.
+constexpr int PANEL = 4;
+
+// v[i] <- the sum of v[i] over the workgroup, i < 8
+__device__ inline void block_sum8(double *v, double *red) {
+    const double s = wave_sum8(v);
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    if (!(lane & 7)) red[(threadIdx.x >> 6) * 8 + (lane >> 3)] = s;
     __syncthreads();
-    double A = 0, B = 0;
-    for (int i = 0; i < nw; i++) { A += red[2 * i]; B += red[2 * i + 1]; }
-    return make_double2(A, B);
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = red[i];
+    for (int w = 1; w < nw; w++)
+#pragma unroll
+        for (int i = 0; i < 8; i++) v[i] += red[w * 8 + i];
 }
 
-__global__ __launch_bounds__(TPB) void build_P_reg_kernel(int V, int Va, int N, const int *__restrict__ agg_sites,
-                                                          double2 *__restrict__ P, int *__restrict__ flag) {
-    __shared__ double red[2][2 * (TPB / 64)];
+__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(2))) void build_P_panel_kernel(
+    int V, int Va, int N, const int *__restrict__ agg_sites, double2 *__restrict__ P, int *__restrict__ flag) {
+    __shared__ double red[2][8 * (TPB / 64)];
     const int a = blockIdx.x, chi = blockIdx.y;
     const bool active = (int)threadIdx.x < Va;
     const int d = active ? agg_sites[(size_t)a * Va + threadIdx.x] : 0;
     const size_t fs = (size_t)12 * V;  // field stride
+    double2 *Pd = P + (size_t)6 * chi * V + d;
     int slot = 0;
-    for (int k = 0; k < N; k++) {
-        double2 *wp = P + (size_t)k * fs;
-        double2 w[6];
-        double n0 = 0;
+    auto load = [&](int k, double2 *v) {
 #pragma unroll
-        for (int c = 0; c < 6; c++) {
-            w[c] = active ? wp[(size_t)(6 * chi + c) * V + d] : make_double2(0, 0);
-            n0 += w[c].x * w[c].x + w[c].y * w[c].y;
+        for (int c = 0; c < 6; c++) v[c] = active && k < N ? Pd[(size_t)k * fs + (size_t)c * V] : make_double2(0, 0);
+    };
+    for (int k0 = 0; k0 < N; k0 += PANEL) {
+        double2 w[PANEL][6], q[6], qn[6];
+        double n0[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < PANEL; i++) {
+            load(k0 + i, w[i]);
+#pragma unroll
+            for (int c = 0; c < 6; c++) n0[i] += w[i][c].x * w[i][c].x + w[i][c].y * w[i][c].y;
         }
-        n0 = block_sum2_1(n0, 0, red[slot]).x;
+        if (k0) load(0, q);
+        block_sum8(n0, red[slot]);
         slot ^= 1;
-        double2 q[6], qn[6];
+        for (int j = 0; j < k0; j++) {
+            load(j + 1 < k0 ? j + 1 : j, qn);   // while column j is used
+            double r[2 * PANEL];
 #pragma unroll
-        for (int c = 0; c < 6; c++) q[c] = active && k > 0 ? P[(size_t)(6 * chi + c) * V + d] : make_double2(0, 0);
-        for (int j = 0; j < k; j++) {
-            // prefetch column j + 1 while column j is used
-            const double2 *qp = P + (size_t)(j + 1 < k ? j + 1 : j) * fs;
+            for (int i = 0; i < PANEL; i++) {
+                double2 t = make_double2(0, 0);
 #pragma unroll
-            for (int c = 0; c < 6; c++) qn[c] = active ? qp[(size_t)(6 * chi + c) * V + d] : make_double2(0, 0);
-            double ra = 0, rb = 0;
-#pragma unroll
-            for (int c = 0; c < 6; c++) {
-                ra += q[c].x * w[c].x + q[c].y * w[c].y;
-                rb += q[c].x * w[c].y - q[c].y * w[c].x;
+                for (int c = 0; c < 6; c++) cfmac(t, q[c], w[i][c]);
+                r[2 * i] = t.x;
+                r[2 * i + 1] = t.y;
             }
-            const double2 r = block_sum2_1(ra, rb, red[slot]);
+            block_sum8(r, red[slot]);
             slot ^= 1;
 #pragma unroll
-            for (int c = 0; c < 6; c++) {
-                w[c] = csub(w[c], cmul(r, q[c]));
-                q[c] = qn[c];
+            for (int i = 0; i < PANEL; i++)
+#pragma unroll
+                for (int c = 0; c < 6; c++) cfma(w[i][c], make_double2(-r[2 * i], -r[2 * i + 1]), q[c]);
+#pragma unroll
+            for (int c = 0; c < 6; c++) q[c] = qn[c];
+        }
+#pragma unroll
+        for (int i = 0; i < PANEL; i++) {
+            if (k0 + i >= N) break;
+            // r[2 i]: the norm of column i; the others: its products with the later columns
+            double r[2 * PANEL] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int c = 0; c < 6; c++) r[2 * i] += w[i][c].x * w[i][c].x + w[i][c].y * w[i][c].y;
+#pragma unroll
+            for (int m = i + 1; m < PANEL; m++) {
+                double2 t = make_double2(0, 0);
+#pragma unroll
+                for (int c = 0; c < 6; c++) cfmac(t, w[i][c], w[m][c]);
+                r[2 * m] = t.x;
+                r[2 * m + 1] = t.y;
             }
-        }
-        double nn = 0;
+            block_sum8(r, red[slot]);
+            slot ^= 1;
+            double rkk = sqrt(r[2 * i]);
+            if (!(rkk > 1e-12 * sqrt(n0[i])) || n0[i] == 0.0) {
+                if (threadIdx.x == 0) atomicExch(flag, 1);
+                rkk = 1.0;
+            }
+            const double inv = 1.0 / rkk;
 #pragma unroll
-        for (int c = 0; c < 6; c++) nn += w[c].x * w[c].x + w[c].y * w[c].y;
-        nn = block_sum2_1(nn, 0, red[slot]).x;
-        slot ^= 1;
-        double rkk = sqrt(nn);
-        if (!(rkk > 1e-12 * sqrt(n0)) || n0 == 0.0) {
-            if (threadIdx.x == 0) atomicExch(flag, 1);
-            rkk = 1.0;
-        }
-        const double inv = 1.0 / rkk;
-        if (active) {
+            for (int c = 0; c < 6; c++) w[i][c] = cscale(w[i][c], inv);
 #pragma unroll
-            for (int c = 0; c < 6; c++) wp[(size_t)(6 * chi + c) * V + d] = cscale(w[c], inv);
+            for (int m = i + 1; m < PANEL; m++)
+#pragma unroll
+                for (int c = 0; c < 6; c++)
+                    cfma(w[m][c], make_double2(-r[2 * m] * inv, -r[2 * m + 1] * inv), w[i][c]);
+            if (active) {
+#pragma unroll
+                for (int c = 0; c < 6; c++) Pd[(size_t)(k0 + i) * fs + (size_t)c * V] = w[i][c];
+            }
         }
     }
 }
@@ -517,8 +552,8 @@ int launch_build_P(Ctx *c, const void *tv64) {
     rc = hip_check(c, hipMemsetAsync(flag, 0, sizeof(int), c->stream), "memset");
     if (rc) return rc;
     if (L1.Va <= TPB)
-        build_P_reg_kernel<<<dim3(L1.Vc, 2), TPB, 0, c->stream>>>(g.V, L1.Va, L1.N, L1.agg_sites, (double2 *)L1.P64,
-                                                                  flag);
+        build_P_panel_kernel<<<dim3(L1.Vc, 2), (unsigned)((L1.Va + 63) / 64 * 64), 0, c->stream>>>(
+            g.V, L1.Va, L1.N, L1.agg_sites, (double2 *)L1.P64, flag);
     else
         build_P_kernel<<<dim3(L1.Vc, 2), TPB, 0, c->stream>>>(g.V, L1.Va, L1.N, L1.agg_sites, (double2 *)L1.P64, flag);
     rc = hip_check(c, hipGetLastError(), "build_P kernel");
