@@ -13,9 +13,13 @@
 // vectors are small (2N complex per coarse site), so the step count of
 // launches, not bandwidth, decides the time. Every sum runs in a fixed order,
 // and every workgroup that needs a coefficient adds the same partials in the
-// same order, so results are deterministic.
+// same order, so results are deterministic. The FP32 coarse GMRES on a compact
+// D_c runs in arnoldi_compact.hip, unless its workspace has no room for the
+// vectors of those kernels; the kernels here serve that case, FP64 and the
+// level-3 operator.
 #include "blas.h"
 #include "coarse.h"
+#include "lanes.h"
 #include "transfer.h"
 
 namespace mgdd {
@@ -420,101 +424,74 @@ int launch_coarse_arnoldi(Ctx *c, const StencilOp &op, int p, int m, int nb, con
 // device, one workgroup (one wave) per right-hand side s. The (m+1) x m
 // Hessenberg matrix (column j: h1 + h2 in rows 0..j, sqrt(nr[j+1]) in row
 // j+1) is cut at the first zero subdiagonal entry (k columns) and reduced
-// to upper triangular form by Givens rotations: lane 0 forms rotation j from
-// column j and applies it to g = beta e_1, the lanes owning the later
-// columns apply it to theirs. y then solves the triangular system (lane 0,
-// back substitution), coef[i][s] = y_i for i < k and 0 for the rest; all 0
-// when beta = sqrt(nr[0]) is 0. A non-finite beta or y sets *status (if
-// given) to 1.
+// to upper triangular form by rotations [conj(c) s; -s c] with c = a / r
+// complex, s = b / r real (b, the subdiagonal entry, is real), r^2 = |a|^2 +
+// b^2: one reciprocal square root each, and the diagonal becomes the real r.
+// Lane l owns column l, lane m the right-hand side g = beta e_1, in LDS; every
+// lane forms the rotation itself and applies it to its own column, so that one
+// wave runs without a barrier. y follows from the last row up, a sum over the
+// lanes per row; coef[i][s] = y_i for i < k and 0 for the rest; all 0 when
+// beta = sqrt(nr[0]) is 0. A non-finite beta or y sets *status (if given) to 1.
+// Bound: the chain of m rotations. 12 steps: 10 us; 18 us with one lane
+// forming the rotations (two hypot and two divisions) between barriers.
 __device__ inline double2 zmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-__device__ inline double2 zconj(double2 a) { return make_double2(a.x, -a.y); }
 
 __global__ __launch_bounds__(64) void hessenberg_lsq_kernel(int m, int nb, const double2 *__restrict__ h1,
                                                             const double2 *__restrict__ h2,
                                                             const double2 *__restrict__ nr, double2 *__restrict__ coef,
                                                             int *__restrict__ status) {
-    __shared__ double2 R[LSQ_MAX_STEPS][LSQ_MAX_STEPS + 2];   // [column][row]
-    __shared__ double2 g[LSQ_MAX_STEPS + 1], y[LSQ_MAX_STEPS];
-    __shared__ double rot_c;
-    __shared__ double2 rot_s;
+    constexpr int LD = LSQ_MAX_STEPS + 3;
+    __shared__ double2 R[(LSQ_MAX_STEPS + 1) * LD];   // [column][row], then g
+    __shared__ double rinv[LSQ_MAX_STEPS];
     const int s = blockIdx.x, l = threadIdx.x;
-    const double beta = sqrt(nr[s].x);
+    const double sub = l <= m ? nr[(size_t)l * nb + s].x : 0.0;   // squared norms, beta^2 in lane 0
+    double2 *col = R + (size_t)(l <= m ? l : m) * LD;
+    if (l < m) {
+        const size_t cj = (size_t)l * (m + 1) * nb + s;
+        for (int i = 0; i <= l; i++) col[i] = cadd(h1[cj + (size_t)i * nb], h2[cj + (size_t)i * nb]);
+    }
+    const double beta = sqrt(__shfl(sub, 0, 64)), below = __shfl(sub, l + 1 < 64 ? l + 1 : 63, 64);
     if (!(beta > 0.0) || !isfinite(beta)) {   // zero start vector: x = 0
         if (l < m) coef[(size_t)l * nb + s] = make_double2(0, 0);
         if (l == 0 && status && !isfinite(beta)) *status = 1;
         return;
     }
-    int k = m;
-    for (int j = 0; j < m; j++) {
-        const double v = nr[(size_t)(j + 1) * nb + s].x;
-        if (l == 0 && status && isnan(v)) *status = 1;
-        if (!(v > 0.0)) { k = j + 1; break; }
-    }
-    if (l < k) {
-        const size_t cj = (size_t)l * (m + 1) * nb;
-        for (int i = 0; i <= l; i++) {
-            const double2 a = h1[cj + (size_t)i * nb + s], b = h2[cj + (size_t)i * nb + s];
-            R[l][i] = make_double2(a.x + b.x, a.y + b.y);
-        }
-        R[l][l + 1] = make_double2(sqrt(fmax(nr[(size_t)(l + 1) * nb + s].x, 0.0)), 0.0);
-    }
-    if (l <= k) g[l] = make_double2(l == 0 ? beta : 0.0, 0.0);
-    __syncthreads();
+    // the first column without a positive subdiagonal entry is the last one
+    const unsigned long long stop = __ballot(l < m && !(below > 0.0));
+    const int k = stop ? __builtin_ctzll(stop) + 1 : m;
+    if (__ballot(l < k && isnan(below)) && l == 0 && status) *status = 1;
+    if (l < m) col[l + 1] = make_double2(sqrt(fmax(below, 0.0)), 0);
+    if (l == m)
+        for (int i = 0; i <= m; i++) col[i] = make_double2(i == 0 ? beta : 0.0, 0);
+    wave_lds_sync();
     for (int j = 0; j < k; j++) {
-        if (l == 0) {
-            const double2 a = R[j][j], b = R[j][j + 1];
-            const double aa = hypot(a.x, a.y), bb = hypot(b.x, b.y);
-            double cr;
-            double2 sr, rho;
-            if (bb == 0.0) {
-                cr = 1.0; sr = make_double2(0, 0); rho = a;
-            } else if (aa == 0.0) {
-                cr = 0.0; sr = make_double2(1, 0); rho = b;
-            } else {
-                const double r = hypot(aa, bb);
-                const double2 ph = make_double2(a.x / aa, a.y / aa);
-                cr = aa / r;
-                const double2 t = zmul(ph, zconj(b));
-                sr = make_double2(t.x / r, t.y / r);
-                rho = make_double2(ph.x * r, ph.y * r);
-            }
-            R[j][j] = rho;
-            R[j][j + 1] = make_double2(0, 0);
-            const double2 gj = g[j];
-            g[j] = make_double2(cr * gj.x, cr * gj.y);
-            const double2 t = zmul(zconj(sr), gj);
-            g[j + 1] = make_double2(-t.x, -t.y);
-            rot_c = cr;
-            rot_s = sr;
+        const double2 a = R[j * LD + j], x = col[j], y = col[j + 1];
+        const double b = R[j * LD + j + 1].x;
+        const double q = 1.0 / sqrt(a.x * a.x + a.y * a.y + b * b);
+        const double2 c = make_double2(a.x * q, a.y * q);
+        const double sn = b * q;
+        wave_lds_sync();
+        if (l >= j && (l < k || l == m)) {
+            // conj(c) x + s y, c y - s x
+            const double2 u = cmulc(c, x), v = zmul(c, y);
+            col[j] = make_double2(u.x + sn * y.x, u.y + sn * y.y);
+            col[j + 1] = make_double2(v.x - sn * x.x, v.y - sn * x.y);
         }
-        __syncthreads();
-        if (l > j && l < k) {
-            const double cr = rot_c;
-            const double2 sr = rot_s, a = R[l][j], b = R[l][j + 1];
-            const double2 u = zmul(sr, b), v = zmul(zconj(sr), a);
-            R[l][j] = make_double2(cr * a.x + u.x, cr * a.y + u.y);
-            R[l][j + 1] = make_double2(cr * b.x - v.x, cr * b.y - v.y);
-        }
-        __syncthreads();
+        if (l == 0) rinv[j] = q;
+        wave_lds_sync();
     }
-    if (l == 0) {
-        bool ok = true;
-        for (int i = k - 1; i >= 0; i--) {
-            double2 t = g[i];
-            for (int q = i + 1; q < k; q++) {
-                const double2 u = zmul(R[q][i], y[q]);
-                t = make_double2(t.x - u.x, t.y - u.y);
-            }
-            const double2 d = R[i][i];
-            const double dn = d.x * d.x + d.y * d.y;
-            const double2 yi = make_double2((t.x * d.x + t.y * d.y) / dn, (t.y * d.x - t.x * d.y) / dn);
-            y[i] = yi;
-            ok = ok && isfinite(yi.x) && isfinite(yi.y);
-        }
-        if (!ok && status) *status = 1;
+    double2 yl = make_double2(0, 0);
+    bool ok = true;
+    for (int i = k - 1; i >= 0; i--) {
+        const double2 r = col[i], g = R[m * LD + i];
+        const double2 u = l > i && l < k ? zmul(r, yl) : make_double2(0, 0);
+        const double q = rinv[i];
+        const double2 yi = make_double2((g.x - wave_sum1(u.x)) * q, (g.y - wave_sum1(u.y)) * q);
+        ok = ok && isfinite(yi.x) && isfinite(yi.y);
+        if (l == i) yl = yi;
     }
-    __syncthreads();
-    if (l < m) coef[(size_t)l * nb + s] = l < k ? y[l] : make_double2(0, 0);
+    if (l == 0 && !ok && status) *status = 1;
+    if (l < m) coef[(size_t)l * nb + s] = yl;
 }
 
 // The same two passes for up to 64 vectors (the long Arnoldi runs of the

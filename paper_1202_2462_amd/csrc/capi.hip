@@ -754,7 +754,7 @@ int mgdd_coarse_solve_noalloc(mgdd_ctx *ctx, int prec, int nrhs, int iters, cons
     Ctx *c = &ctx->c;
     void *base = (c->dev >= 0 && c->dev < NOALLOC_MAX_DEVICES) ? scratch_dev[c->dev] : nullptr;
     if (!base) return fail(c, MGDD_ENOTREADY, "no scratch array on this device");
-    const size_t need = coarse_gmres_bytes(c, prec, iters, nrhs) + 256;
+    const size_t need = coarse_gmres_min_bytes(c, prec, iters, nrhs) + 256;
     if (need > NOALLOC_SCRATCH_BYTES)
         return fail(c, MGDD_EINVAL,
                     "the allocation-free coarse solve needs " + std::to_string(need) + " bytes of scratch, more than its " +

@@ -65,4 +65,11 @@ template <typename T> __device__ inline T wave_sum1(T v) {
     return sum_of_8(v);
 }
 
+// LDS written by lanes of this wave is read by others of it after this
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace mgdd

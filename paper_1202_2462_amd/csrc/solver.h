@@ -34,11 +34,14 @@ struct MgOpts {
 MgOpts mg_opts(const mgdd_solve_params *sp);
 
 // nb: number of right-hand sides handled together (stacked fields)
+// bytes the coarse GMRES wants, and the least it runs with
 size_t coarse_gmres_bytes(const Ctx *c, int p, int m, int nb);
+size_t coarse_gmres_min_bytes(const Ctx *c, int p, int m, int nb);
 size_t precond_bytes(const Ctx *c, int p, const MgOpts &o, int nb);
 size_t solve_bytes(const Ctx *c, const mgdd_solve_params *sp, int nb);
 int coarse_gmres(Ctx *c, int p, int m, int nb, const void *b, void *x, Arena &A, int *status = nullptr);
 size_t stencil_gmres_bytes(const StencilOp &op, int p, int m, int nb);
+size_t stencil_gmres_min_bytes(const StencilOp &op, int p, int m, int nb);
 int stencil_gmres(Ctx *c, const StencilOp &op, int p, int m, int nb, const void *b, void *x, Arena &A,
                   int *status = nullptr);
 int mg_precond(Ctx *c, int p, int nb, const void *r64, void *z, const MgOpts &o, Arena &A);

@@ -255,11 +255,25 @@ static int hessenberg_combine(Ctx *c, int p, int m, int nb, size_t n, const doub
 // ---------------------------------------------------------------- coarse GMRES
 
 size_t coarse_gmres_bytes(const Ctx *c, int p, int m, int nb) { return stencil_gmres_bytes(level1_op(c), p, m, nb); }
+size_t coarse_gmres_min_bytes(const Ctx *c, int p, int m, int nb) {
+    return stencil_gmres_min_bytes(level1_op(c), p, m, nb);
+}
 
-size_t stencil_gmres_bytes(const StencilOp &op, int p, int m, int nb) {
+// scratch of the Arnoldi steps that read every block of a compact D_c once
+// (0: not for this operator, precision or step count)
+static size_t compact_scratch(const StencilOp &op, int p, int m, int nb) {
+    return p == MGDD_F32 && op.H32 && m <= ARNOLDI_FUSED_MAX_STEPS ? compact_arnoldi_scratch(op, m, nb) : 0;
+}
+
+size_t stencil_gmres_min_bytes(const StencilOp &op, int p, int m, int nb) {
     size_t n = (size_t)op.V * 2 * op.N * nb;
     return (size_t)(m + 3) * (n * csize(p) + 256) + (4 * (size_t)(m + 2) * (m + 2) + 2 * (size_t)(m + 2)) * nb * 16 +
            coarse_arnoldi_scratch(op, m, nb) + 8192;
+}
+
+size_t stencil_gmres_bytes(const StencilOp &op, int p, int m, int nb) {
+    const size_t old = coarse_arnoldi_scratch(op, m, nb), cs = compact_scratch(op, p, m, nb);
+    return stencil_gmres_min_bytes(op, p, m, nb) + (cs > old ? cs - old : 0);
 }
 
 int coarse_gmres(Ctx *c, int p, int m, int nb, const void *b, void *x, Arena &A, int *status) {
@@ -286,11 +300,15 @@ int stencil_gmres(Ctx *c, const StencilOp &op, int p, int m, int nb, const void 
     if (!coef) return fail(c, MGDD_ENOMEM, "coarse GMRES workspace");
     int rc = MGDD_OK;
     if (m <= ARNOLDI_FUSED_MAX_STEPS) {
-        // three fused kernels per Arnoldi step
         void *w2 = A.take(n * nb * cs);
-        void *scr = A.take(coarse_arnoldi_scratch(op, m, nb));
+        // the steps on a compact D_c take four more vectors; a caller's fixed
+        // workspace that holds the others but not these gets the general ones
+        const size_t compact = compact_scratch(op, p, m, nb);
+        const bool fits = compact && A.off + compact + 256 <= A.cap;
+        void *scr = A.take(fits ? compact : coarse_arnoldi_scratch(op, m, nb));
         if (!scr) return fail(c, MGDD_ENOMEM, "coarse GMRES workspace");
-        rc = launch_coarse_arnoldi(c, op, p, m, nb, b, V.data(), w, w2, scr, h1, h2, nr);
+        rc = fits ? launch_compact_arnoldi(c, op, m, nb, b, V.data(), w, w2, scr, h1, h2, nr)
+                  : launch_coarse_arnoldi(c, op, p, m, nb, b, V.data(), w, w2, scr, h1, h2, nr);
     } else {
         const void *bp = b;
         rc = blas_multidot(c, p, p, n, &bp, 1, b, nr, nb);

@@ -56,6 +56,11 @@ int launch_coarse_apply(Ctx *c, int prec, int nrhs, const void *in, void *out);
 // Fused Arnoldi process on D_c for the coarse GMRES (arnoldi.hip); m <= 15.
 constexpr int ARNOLDI_FUSED_MAX_STEPS = 15;
 size_t coarse_arnoldi_scratch(const StencilOp &op, int m, int nb);
+// The same on a compact FP32 D_c (op.H32) with every block read once per step
+// (arnoldi_compact.hip); scratch: compact_arnoldi_scratch bytes.
+size_t compact_arnoldi_scratch(const StencilOp &op, int m, int nb);
+int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const void *b, void *const *V, void *work0,
+                           void *work1, void *scratch, double2 *H1, double2 *H2, double2 *NR);
 // w <- w - V V^H w twice (nb segments of n), three passes; k <= 64 vectors.
 constexpr int FUSED_CGS2_MAX = 64;
 int fused_cgs2(Ctx *c, int p, size_t n, int nb, void *const *V, int k, void *w, double2 *h1, double2 *h2,
