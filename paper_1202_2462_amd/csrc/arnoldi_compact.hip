@@ -16,12 +16,14 @@
 //           and the norm from the previous step's sums (the second pass of
 //           step j - 1), then the products with the blocks of a, and the sums
 //           of <v_k, D_c v_j>, taken with yf at a and with t_mu at a + mu;
-//   pass:   y = yf + sum t - V h1, sums of <v_k, y> and |y|^2.
+//   pass:   y = yf + sum t - V h1 (in double), sums of <v_k, y> and |y|^2.
 // With |y|^2 = |y - V h2|^2 + |h2|^2 for the orthonormal V no third kernel has
-// to form the norm. Several right-hand sides take four: the products on the
-// matrix cores, then three passes (gather, first and second projection).
-#include <utility>
-
+// to form the norm. Several right-hand sides take four: v_j, the products on
+// the matrix cores, the sums of <v_k, yf + sum t>, the first projection.
+// Both forms do the same arithmetic in FP32, operation by operation, so that a
+// right-hand side gets the same result alone and among others: a 16x16x4 FP32
+// MFMA is the chain of fused multiply-adds over its four summation indices in
+// ascending order (checked on the card), and the stream kernel sums in fours.
 #include "lanes.h"
 #include "stencil.h"
 #include "transfer.h"
@@ -32,7 +34,6 @@ namespace {
 
 constexpr int NVMAX = 16;        // basis vectors of a cycle
 constexpr int STPB = 256;        // threads of the stream kernel
-constexpr int SCOL = 4;          // columns a thread of the stream kernel loads at once
 constexpr int PTPB = 512;        // threads of the pass kernel
 constexpr int PGRID = 256;       // workgroups of a pass per right-hand side, at most
 
@@ -68,54 +69,72 @@ __device__ inline void sum_quantities(const double2 *__restrict__ part, size_t s
     __syncthreads();
 }
 
+// |y - V h2|^2 from |y|^2 (the last quantity) and h2
+__device__ inline double rest_norm(const double2 *coef, int nk) {
+    double nn = coef[nk].x;
+#pragma unroll 1
+    for (int k = 0; k < nk; k++) nn -= coef[k].x * coef[k].x + coef[k].y * coef[k].y;
+    return nn;
+}
+
+// Both products sum in batches of four: a batch of the row sums is four
+// consecutive columns of one block (the blocks' batches form one list of 5 nb4,
+// nb4 = ceil(n2 / 4)), CHAIN consecutive batches are added up, then these in
+// four interleaved sums; a batch of the column sums is four rows, added in
+// order.
+__host__ __device__ inline int row_groups(int n2) { return (n2 + 3) >> 2; }
+__host__ __device__ inline int chain_length(int n2) {
+    const int nb4 = row_groups(n2), groups = STPB / nb4;
+    return (5 * nb4 + groups - 1) / groups;
+}
+
 // ---------------------------------------------------------------- one right-hand side
 //
 // One workgroup per coarse site, the workgroups of the grid taking the sites
-// in turn. Thread (cg, rg) takes the rows 4 rg .. 4 rg + 3 of the columns cg,
-// cg + CG, ... of the site's 5 blocks (column-major, one list of 5 n2
-// columns): a column of 4 rows is 32 contiguous bytes, read once and used for
-// both products; the row sums are added over cg, the column sums over rg,
-// through LDS. hin: h2 and the squared norm of the previous step ([j + 1][nin]
-// partials, the norm last; for j = 0 only the norm of w).
+// in turn. Thread (cg, rg) takes the rows 4 rg .. 4 rg + 3 of chain cg of the
+// column batches of the site's 5 blocks (column-major): a column of 4 rows is
+// 32 contiguous bytes, read once and used for both products; the row sums are
+// added over cg, the column sums over rg, through LDS. hin: h2 and the squared
+// norm of the previous step ([j + 1][nin] partials, the norm last; for j = 0
+// only the norm of w).
 // Bound: reading the blocks (524 MB at 8^3 x 16 coarse sites, N = 20, 103 us at
 // the 5.1 TB/s of a large copy): 126 us there, and 11 to 20 us the pass, where
 // forming each site's backward hops from its neighbours' blocks took 168 us,
 // two passes of 15 us and two sums of 11 us. At 4^3 x 8 sites the chain of
 // loads and sums decides: 12.3 and 6 to 11 us against 11.8, 7.9 and 7.9.
-__global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void arnoldi_stream_kernel(int Vc, int N, const int *__restrict__ cnbr,
-                                                              const float2 *__restrict__ H,
-                                                              const float2 *__restrict__ w,
-                                                              const double2 *__restrict__ hin, int nin, Basis V, int j,
-                                                              float2 *__restrict__ vj, float2 *__restrict__ yf,
-                                                              float2 *__restrict__ t, double2 *__restrict__ part,
-                                                              double2 *__restrict__ h2, double2 *__restrict__ nr) {
+__global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void arnoldi_stream_kernel(
+    int Vc, int N, const int *__restrict__ cnbr, const float2 *__restrict__ H, const float2 *__restrict__ w,
+    const double2 *__restrict__ hin, int nin, Basis V, int j, float2 *__restrict__ vj, float2 *__restrict__ yf,
+    float2 *__restrict__ t, double2 *__restrict__ part, double2 *__restrict__ h2, double2 *__restrict__ nr) {
     extern __shared__ float2 sm[];
     __shared__ double2 coef[NVMAX];
-    const int n2 = 2 * N, n5 = 5 * n2, NR = (n2 + 3) >> 2, CG = STPB / NR, tid = threadIdx.x;
+    const int n2 = 2 * N, n5 = 5 * n2, NR = row_groups(n2), NBT = 5 * NR, M = chain_length(n2), tid = threadIdx.x;
+    const int CG = (NBT + M - 1) / M;       // chains
     float2 *vs = sm;                        // [j + 1][5 n2]: v_k at a and its forward neighbours
     float2 *us = vs + (size_t)(j + 1) * n5; // [5 n2]: yf(a) and t_mu(a)
     float2 *yp = us + n5;                   // [CG][n2]
     float2 *tp = yp + CG * n2;              // [4 n2][NR]
-    const int cg = tid / NR, rg = tid % NR, row = 4 * rg;
+    const int cg = tid / NR, rg = tid - cg * NR, row = 4 * rg;
     const bool active = cg < CG;
     const size_t blk = (size_t)n2 * n2;
-    // SCOL columns of the thread's rows, from column c0 = cg + c1 on, through a
-    // buffer resource over the site's blocks: columns past the end read as 0
-    // (rows past n2, where that is no multiple of 4, are of the next column;
-    // the sums below leave them out)
-    const unsigned vo = (unsigned)(cg * n2 + row) * 8u;
-    auto columns = [&](int a, int c1, v4f (&f)[SCOL][2]) {
+    // the four columns of batch m (4 rows each) through a buffer resource over
+    // the site's blocks: past the end reads as 0 (rows past n2 and columns past
+    // a block, where n2 is no multiple of 4, are others that the sums below
+    // leave out)
+    auto columns = [&](int a, int m, v4f (&f)[4][2]) {
         const rsrc_t B = make_rsrc(H + (size_t)a * 5 * blk, 5 * blk * 8);
+        const int b = m / NR;
+        const unsigned vo = (unsigned)((b * n2 + 4 * (m - b * NR)) * n2 + row) * 8u;
 #pragma unroll
-        for (int q = 0; q < SCOL; q++) {
-            const unsigned so = (unsigned)((c1 + q * CG) * n2) * 8u;
+        for (int q = 0; q < 4; q++) {
+            const unsigned so = (unsigned)(q * n2) * 8u;
             f[q][0] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(B, vo, so, 0));
             f[q][1] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(B, vo + 16u, so, 0));
         }
     };
     // in flight while the sums are taken and v_j is formed
-    v4f f[SCOL][2];
-    columns(__builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, Vc)), 0, f);
+    v4f f[4][2];
+    columns(__builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, Vc)), cg * M, f);
     const int wave = tid >> 6, lane = tid & 63;
     double sc = 0;
     double2 acc[4];
@@ -139,9 +158,7 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
         }
         if (l == (int)blockIdx.x) {
             sum_quantities<STPB / 64>(hin, (size_t)nin, j + 1, nin, coef);
-            double nn = coef[j].x;
-#pragma unroll 1
-            for (int k = 0; k < j; k++) nn -= coef[k].x * coef[k].x + coef[k].y * coef[k].y;
+            const double nn = rest_norm(coef, j);
             sc = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
             if (blockIdx.x == 0) {
                 if (tid == 0) nr[0] = make_double2(nn, 0);
@@ -173,33 +190,54 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
                 x4[r] = row + r < n2 ? x[row + r] : make_float2(0.f, 0.f);
                 if (row + r >= N) x4[r] = cneg(x4[r]);
             }
-            for (int c1 = 0; c1 < n5; c1 += SCOL * CG) {
-                if (c1) columns(a, c1, f);
-                // the batch's row sums by themselves, then added: shorter chains in FP32
-                float2 z4[4] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f), make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
+            for (int i = 0; i < M; i++) {
+                const int m = cg * M + i;
+                if (m >= NBT) break;
+                if (i) columns(a, m, f);
+                const int b = m / NR, c0 = 4 * (m - b * NR);   // first column of the batch in block b
+                float2 xc[4];
 #pragma unroll
-                for (int q = 0; q < SCOL; q++) {
-                    const int c = c1 + q * CG + cg;
-                    if (c >= n5) continue;
-                    const float2 b[4] = {make_float2(f[q][0][0], f[q][0][1]), make_float2(f[q][0][2], f[q][0][3]),
-                                         make_float2(f[q][1][0], f[q][1][1]), make_float2(f[q][1][2], f[q][1][3])};
-                    const float2 xc = x[c];
-                    float2 s = make_float2(0.f, 0.f);
+                for (int q = 0; q < 4; q++) xc[q] = c0 + q < n2 ? x[b * n2 + c0 + q] : make_float2(0.f, 0.f);
+                // F(row + r, c0 + q)
+                auto F = [&](int q, int r) { return make_float2(f[q][r >> 1][2 * (r & 1)], f[q][r >> 1][2 * (r & 1) + 1]); };
 #pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        cfma(z4[r], b[r], xc);
-                        cfmac(s, b[r], x4[r]);
+                for (int r = 0; r < 4; r++) {
+                    float2 z = make_float2(0.f, 0.f);
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        z.x = fmaf(F(q, r).x, xc[q].x, z.x);
+                        z.y = fmaf(F(q, r).x, xc[q].y, z.y);
                     }
-                    if (c >= n2) tp[(c - n2) * NR + rg] = s;
-                }
 #pragma unroll
-                for (int r = 0; r < 4; r++) y4[r] = cadd(y4[r], z4[r]);
+                    for (int q = 0; q < 4; q++) {
+                        z.x = fmaf(-F(q, r).y, xc[q].y, z.x);
+                        z.y = fmaf(F(q, r).y, xc[q].x, z.y);
+                    }
+                    y4[r] = cadd(y4[r], z);
+                }
+                if (b)
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        float2 z = make_float2(0.f, 0.f);
+#pragma unroll
+                        for (int r = 0; r < 4; r++) {
+                            z.x = fmaf(F(q, r).x, x4[r].x, z.x);
+                            z.y = fmaf(F(q, r).x, x4[r].y, z.y);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; r++) {
+                            z.x = fmaf(F(q, r).y, x4[r].y, z.x);
+                            z.y = fmaf(-F(q, r).y, x4[r].x, z.y);
+                        }
+                        if (c0 + q < n2) tp[((b - 1) * n2 + c0 + q) * NR + rg] = z;
+                    }
             }
 #pragma unroll
             for (int r = 0; r < 4; r++)
                 if (row + r < n2) yp[cg * n2 + row + r] = y4[r];
         }
-        if (l + (int)gridDim.x < Vc) columns(__builtin_amdgcn_readfirstlane(xcd_remap(l + gridDim.x, Vc)), 0, f);   // the next site's
+        if (l + (int)gridDim.x < Vc)   // the next site's
+            columns(__builtin_amdgcn_readfirstlane(xcd_remap(l + gridDim.x, Vc)), cg * M, f);
         __syncthreads();
         // four lanes a row of yf, one thread an entry of t (4 n2 <= 256 of each)
         if (tid < 4 * n2) {
@@ -248,14 +286,15 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
 // The same products on the matrix cores (16x16x4 FP32 MFMA, complex products as
 // four real ones), one workgroup per (coarse site, 16 right-hand sides): the
 // blocks pass through LDS one after the other (the next one's loads in
-// flight; one buffer, so that three workgroups share a CU), where wave w < nt reads the rows of tile w for yf and wave nt + w
-// the columns of tile w for t_mu. Operand layouts as in the coarse apply: A
-// [i][k] in lane i + 16 k, B[k][j] in lane j + 16 k, result register v of lane
-// l holds row 4 (l / 16) + v of column l % 16. v_j = w / |w| is formed here.
+// flight; one buffer, so that three workgroups share a CU), where wave w < nt
+// reads the rows of tile w for yf and wave nt + w the columns of tile w for
+// t_mu. Operand layouts as in the coarse apply: A [i][k] in lane i + 16 k,
+// B[k][j] in lane j + 16 k, result register v of lane l holds row 4 (l / 16) +
+// v of column l % 16. One MFMA is one batch of the stream kernel's sums.
 // Bound: the latency of each block's way through LDS (matrix cores 34 %, vector
-// units 28 % busy). 6^3 x 12 coarse sites, N = 24, 12 right-hand sides: 144 us
-// and three passes of 19 to 39 us; reading the blocks once per right-hand side
-// took 725 us and two passes of 92 us.
+// units 28 % busy). 6^3 x 12 coarse sites, N = 24, 12 right-hand sides: 169 us,
+// and 48 to 117 us the other three kernels; reading the blocks once per
+// right-hand side took 725 us and two passes of 92 us.
 __device__ inline v4f mma(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // LDS row lengths in complex numbers: 2 more than a multiple of 16, so that
@@ -264,13 +303,10 @@ __host__ __device__ inline int mfma_ldx(int n2) { return (5 * n2 + 15) / 16 * 16
 __host__ __device__ inline int mfma_ldb(int n2) { return (n2 + 15) / 16 * 16 + 2; }
 
 __global__ __launch_bounds__(512) void arnoldi_mfma_kernel(int Vc, int N, int nb, const int *__restrict__ cnbr,
-                                                           const float2 *__restrict__ H, const float2 *__restrict__ w,
-                                                           const double2 *__restrict__ npart, int nnp,
-                                                           float2 *__restrict__ vj, float2 *__restrict__ yf,
-                                                           float2 *__restrict__ t, double2 *__restrict__ nr) {
+                                                           const float2 *__restrict__ H, const float2 *__restrict__ vj,
+                                                           float2 *__restrict__ yf, float2 *__restrict__ t) {
     extern __shared__ float2 sm[];
-    __shared__ double norm[16];
-    const int n2 = 2 * N, n5 = 5 * n2, nt = (n2 + 15) >> 4, LX = mfma_ldx(n2), LB = mfma_ldb(n2);
+    const int n2 = 2 * N, nt = (n2 + 15) >> 4, LX = mfma_ldx(n2), LB = mfma_ldb(n2), M = chain_length(n2);
     float2 *X = sm;                          // [16 rhs][LX]: v at a and its forward neighbours
     float2 *buf = X + 16 * LX;               // the block at hand, [n2 columns][LB]
     const int a = xcd_block(gridDim.x), r0 = blockIdx.y * 16, tid = threadIdx.x, T = blockDim.x;
@@ -284,18 +320,6 @@ __global__ __launch_bounds__(512) void arnoldi_mfma_kernel(int Vc, int N, int nb
         const int p = tid + q * T;
         f[q] = B[p < npair ? p : npair - 1];
     }
-    // squared norms of this tile's right-hand sides, one wave each
-    for (int r = wave; r < 16; r += T >> 6) {
-        double s = 0;
-        if (r0 + r < nb)
-            for (int g = lane; g < nnp; g += 64) s += npart[(size_t)(r0 + r) * nnp + g].x;
-        s = wave_sum1(s);
-        if (lane == 0) {
-            norm[r] = s > 0 ? 1.0 / sqrt(s) : 0.0;
-            if (a == 0 && r0 + r < nb) nr[r0 + r] = make_double2(s, 0);
-        }
-    }
-    __syncthreads();
     // one wave per vector (n2 <= 64), eight in flight
     const int nw = T >> 6, li = lane < n2 ? lane : n2 - 1;
     for (int p0 = wave; p0 < 80; p0 += 8 * nw) {
@@ -309,22 +333,32 @@ __global__ __launch_bounds__(512) void arnoldi_mfma_kernel(int Vc, int N, int nb
 #pragma unroll
         for (int u = 0; u < 8; u++) {
             const int p = p0 + u * nw < 80 ? p0 + u * nw : 79, r = r0 + p / 5;
-            v[u] = w[((size_t)(r < nb ? r : nb - 1) * Vc + at[u]) * n2 + li];
+            v[u] = vj[((size_t)(r < nb ? r : nb - 1) * Vc + at[u]) * n2 + li];
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < 8; u++) {
             const int p = p0 + u * nw, r = p / 5, dd = p - 5 * r;
-            if (p < 80 && lane < n2) {
-                const float2 x = r0 + r < nb ? cscale(v[u], (float)norm[r]) : make_float2(0.f, 0.f);
-                if (!dd && r0 + r < nb) vj[((size_t)(r0 + r) * Vc + a) * n2 + lane] = x;
-                X[r * LX + dd * n2 + lane] = x;
-            }
+            if (p < 80 && lane < n2) X[r * LX + dd * n2 + lane] = r0 + r < nb ? v[u] : make_float2(0.f, 0.f);
         }
     }
-    // the sums of each block by themselves, then added: shorter chains in FP32
     const v4f zero = {0, 0, 0, 0};
-    v4f yre = zero, yim = zero;
+    // row sums: the current chain, and four interleaved sums of chains
+    v4f cre = zero, cim = zero, sre[4], sim[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) sre[q] = sim[q] = zero;
+    int left = M, chain = 0;
+    auto end_chain = [&]() {
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            if ((chain & 3) == q) {
+                sre[q] += cre;
+                sim[q] += cim;
+            }
+        cre = cim = zero;
+        left = M;
+        chain++;
+    };
     const bool forward = wave < nt, rhs_ok = r0 + lo < nb;
     const int tile = (forward ? wave : wave - nt) * 16, rc = tile + lo < n2 ? tile + lo : n2 - 1;
     const float2 *Xr = X + lo * LX;
@@ -346,75 +380,116 @@ __global__ __launch_bounds__(512) void arnoldi_mfma_kernel(int Vc, int N, int nb
             }
         }
         __syncthreads();
-        v4f re0 = zero, re1 = zero, im0 = zero, im1 = zero;
+        // entry k of the batch from k0 on: A the block's, x the vector's, 0 past n2
         if (forward) {
-            for (int k0 = 0; k0 < n2; k0 += 8) {
-                float2 A[2], x[2];
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    const int k = k0 + 4 * u + hi, kc = k < n2 ? k : n2 - 1;
-                    A[u] = buf[kc * LB + rc];
-                    x[u] = Xr[b * n2 + kc];
-                    if (k >= n2) x[u] = make_float2(0.f, 0.f);
-                }
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    re0 = mma(A[u].x, x[u].x, re0);
-                    im0 = mma(A[u].x, x[u].y, im0);
-                    re1 = mma(-A[u].y, x[u].y, re1);
-                    im1 = mma(A[u].y, x[u].x, im1);
-                }
+            auto load = [&](int k0, float2 &A, float2 &x) {
+                const int k = k0 + hi, kc = k < n2 ? k : n2 - 1;
+                A = buf[kc * LB + rc];
+                x = Xr[b * n2 + kc];
+                if (k >= n2) x = make_float2(0.f, 0.f);
+            };
+            float2 A, x, An, xn;
+            load(0, A, x);
+            for (int k0 = 0; k0 < n2; k0 += 4) {
+                load(k0 + 4 < n2 ? k0 + 4 : 0, An, xn);
+                v4f re = mma(A.x, x.x, zero), im = mma(A.x, x.y, zero);
+                re = mma(-A.y, x.y, re);
+                im = mma(A.y, x.x, im);
+                cre += re;
+                cim += im;
+                if (!--left) end_chain();
+                A = An;
+                x = xn;
             }
-            yre += re0 + re1;
-            yim += im0 + im1;
         } else if (b > 0) {
-            for (int i0 = 0; i0 < n2; i0 += 8) {
-                float2 A[2], x[2];
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    const int i = i0 + 4 * u + hi, ic = i < n2 ? i : n2 - 1;
-                    A[u] = buf[rc * LB + ic];
-                    x[u] = Xr[ic];
-                    if (i >= N) x[u] = cneg(x[u]);
-                    if (i >= n2) x[u] = make_float2(0.f, 0.f);
-                }
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    re0 = mma(A[u].x, x[u].x, re0);
-                    im0 = mma(A[u].x, x[u].y, im0);
-                    re1 = mma(A[u].y, x[u].y, re1);
-                    im1 = mma(-A[u].y, x[u].x, im1);
-                }
+            auto load = [&](int i0, float2 &A, float2 &x) {
+                const int i = i0 + hi, ic = i < n2 ? i : n2 - 1;
+                A = buf[rc * LB + ic];
+                x = Xr[ic];
+                if (i >= N) x = cneg(x);
+                if (i >= n2) x = make_float2(0.f, 0.f);
+            };
+            v4f ure = zero, uim = zero;
+            float2 A, x, An, xn;
+            load(0, A, x);
+            for (int i0 = 0; i0 < n2; i0 += 4) {
+                load(i0 + 4 < n2 ? i0 + 4 : 0, An, xn);
+                v4f re = mma(A.x, x.x, zero), im = mma(A.x, x.y, zero);
+                re = mma(A.y, x.y, re);
+                im = mma(-A.y, x.x, im);
+                ure += re;
+                uim += im;
+                A = An;
+                x = xn;
             }
-            const v4f re = re0 + re1, im = im0 + im1;
             if (rhs_ok) {
                 float2 *o = t + (((size_t)(r0 + lo) * Vc + a) * 4 + b - 1) * n2;
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
                     const int c = tile + 4 * hi + v;
-                    if (c < n2) o[c] = c < N ? make_float2(re[v], im[v]) : make_float2(-re[v], -im[v]);
+                    if (c < n2) o[c] = c < N ? make_float2(ure[v], uim[v]) : make_float2(-ure[v], -uim[v]);
                 }
             }
         }
     }
     if (forward && rhs_ok) {
+        if (left < M) end_chain();
+        const v4f re = (sre[0] + sre[1]) + (sre[2] + sre[3]), im = (sim[0] + sim[1]) + (sim[2] + sim[3]);
         float2 *o = yf + ((size_t)(r0 + lo) * Vc + a) * n2;
 #pragma unroll
         for (int v = 0; v < 4; v++) {
             const int i = tile + 4 * hi + v;
-            if (i < n2) o[i] = make_float2(yre[v], yim[v]);
+            if (i < n2) o[i] = make_float2(re[v], im[v]);
         }
+    }
+}
+
+// v_j = (y - V h2) / |.| for several right-hand sides, as the stream kernel
+// forms it; stores h2[k nb + segment] and the squared norm
+template <int NV>
+__global__ __launch_bounds__(PTPB) void arnoldi_vector_kernel(int n, Basis V, int nk, const double2 *__restrict__ pin,
+                                                              int npin, const float2 *__restrict__ w,
+                                                              float2 *__restrict__ vj, double2 *__restrict__ h2,
+                                                              double2 *__restrict__ nr) {
+    const int sg = blockIdx.y, nb = gridDim.y, G = gridDim.x, g = blockIdx.x;
+    const size_t so = (size_t)sg * n;
+    __shared__ double2 coef[NVMAX];
+    v4f v[NV], yv;
+    auto load = [&](int e) {
+        yv = *(const v4f *)(w + so + e);
+#pragma unroll
+        for (int k = 0; k < NV; k++) v[k] = k < nk ? *(const v4f *)(V.p[k] + so + e) : (v4f){0, 0, 0, 0};
+    };
+    int e = (g * PTPB + (int)threadIdx.x) * 2;
+    if (e < n) load(e);
+    sum_quantities<PTPB / 64>(pin + (size_t)sg * npin, (size_t)nb * npin, nk + 1, npin, coef);
+    const double nn = rest_norm(coef, nk), sc = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
+    if (g == 0) {
+        if (threadIdx.x == 0) nr[sg] = make_double2(nn, 0);
+        if ((int)threadIdx.x < nk) h2[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
+    }
+    for (; e < n; e += G * PTPB * 2) {
+        double2 r0 = make_double2((double)yv[0], (double)yv[1]), r1 = make_double2((double)yv[2], (double)yv[3]);
+#pragma unroll
+        for (int k = 0; k < NV; k++)
+            if (k < nk) {
+                const double2 h = cneg(coef[k]);
+                cfma(r0, h, make_double2((double)v[k][0], (double)v[k][1]));
+                cfma(r1, h, make_double2((double)v[k][2], (double)v[k][3]));
+            }
+        *(v4f *)(vj + so + e) = (v4f){(float)(r0.x * sc), (float)(r0.y * sc), (float)(r1.x * sc), (float)(r1.y * sc)};
+        if (e + G * PTPB * 2 < n) load(e + G * PTPB * 2);
     }
 }
 
 // ---------------------------------------------------------------- passes over the basis
 //
-// y <- [GATHER: y + sum_mu t_mu(a - mu)] [SUB: - sum_{k < nk} coef_k v_k], coef
-// summed from pin (npin partials each); then the sums of <v_k, y> (DOTS, k <
-// nk) and of |y|^2 (NORM, as quantity nk with DOTS, else 0) of each workgroup
-// into pout [quantity][segment][workgroup]; workgroup 0 stores coef in hout[k
-// nb + segment]. Grid (G, nb).
-template <int NV, bool GATHER, bool SUB, bool DOTS, bool NORM>
+// z = yf + sum_mu t_mu(a - mu) in double [SUB: - sum_{k < nk} coef_k v_k, coef
+// summed from pin (npin partials each), stored in y = yf, in FP32, and coef by
+// workgroup 0 in hout[k nb + segment]]; then the sums of <v_k, z> (k < nk) and,
+// with SUB, of |z|^2 (as quantity nk) of each workgroup into pout
+// [quantity][segment][workgroup]. Grid (G, nb).
+template <int NV, bool SUB>
 __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, const int *__restrict__ cnbr, Basis V,
                                                             int nk, const double2 *__restrict__ pin, int npin,
                                                             float2 *__restrict__ y, const float2 *__restrict__ t,
@@ -426,17 +501,15 @@ __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, cons
     __shared__ double red[PTPB / 64][NQ];
     // two elements (n2 is even: of one site); the first pair is loaded while the
     // coefficients are summed
-    v4f v[NV], yv;
+    v4f v[NV], yv, tv[4];
     auto load = [&](int e) {
         yv = *(const v4f *)(y + so + e);
 #pragma unroll
         for (int k = 0; k < NV; k++) v[k] = k < nk ? *(const v4f *)(V.p[k] + so + e) : (v4f){0, 0, 0, 0};
-        if (GATHER) {
-            const int a = e / n2, i = e - a * n2;
-            const float2 *ts = t + 4 * so + i;
+        const int a = e / n2, i = e - a * n2;
+        const float2 *ts = t + 4 * so + i;
 #pragma unroll
-            for (int mu = 0; mu < 4; mu++) yv += *(const v4f *)(ts + (size_t)(cnbr[a * 9 + 2 + 2 * mu] * 4 + mu) * n2);
-        }
+        for (int mu = 0; mu < 4; mu++) tv[mu] = *(const v4f *)(ts + (size_t)(cnbr[a * 9 + 2 + 2 * mu] * 4 + mu) * n2);
     };
     double acc[NQ];
 #pragma unroll
@@ -448,50 +521,52 @@ __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, cons
         if (g == 0 && (int)threadIdx.x < nk) hout[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
     }
     for (; e < n; e += G * PTPB * 2) {
+        double2 y0 = make_double2((double)yv[0], (double)yv[1]), y1 = make_double2((double)yv[2], (double)yv[3]);
+#pragma unroll
+        for (int mu = 0; mu < 4; mu++) {
+            y0 = cadd(y0, make_double2((double)tv[mu][0], (double)tv[mu][1]));
+            y1 = cadd(y1, make_double2((double)tv[mu][2], (double)tv[mu][3]));
+        }
         if (SUB) {
-            double2 r0 = make_double2((double)yv[0], (double)yv[1]), r1 = make_double2((double)yv[2], (double)yv[3]);
 #pragma unroll
             for (int k = 0; k < NV; k++)
                 if (k < nk) {
                     const double2 h = cneg(coef[k]);
-                    cfma(r0, h, make_double2((double)v[k][0], (double)v[k][1]));
-                    cfma(r1, h, make_double2((double)v[k][2], (double)v[k][3]));
+                    cfma(y0, h, make_double2((double)v[k][0], (double)v[k][1]));
+                    cfma(y1, h, make_double2((double)v[k][2], (double)v[k][3]));
                 }
-            yv = (v4f){(float)r0.x, (float)r0.y, (float)r1.x, (float)r1.y};
-        }
-        *(v4f *)(y + so + e) = yv;
-        if (SUB && DOTS) {
+            yv = (v4f){(float)y0.x, (float)y0.y, (float)y1.x, (float)y1.y};
+            *(v4f *)(y + so + e) = yv;
+            y0 = make_double2((double)yv[0], (double)yv[1]);
+            y1 = make_double2((double)yv[2], (double)yv[3]);
             // the products below widen v again: kept in double it would not fit the registers
 #pragma unroll
             for (int k = 0; k < NV; k++) asm volatile("" : "+v"(v[k]));
         }
-        const double2 y0 = make_double2((double)yv[0], (double)yv[1]), y1 = make_double2((double)yv[2], (double)yv[3]);
-        if (DOTS) {
 #pragma unroll
-            for (int k = 0; k < NV; k++)
-                if (k < nk) {
-                    double2 d = make_double2(acc[2 * k], acc[2 * k + 1]);
-                    cfmac(d, make_double2((double)v[k][0], (double)v[k][1]), y0);
-                    cfmac(d, make_double2((double)v[k][2], (double)v[k][3]), y1);
-                    acc[2 * k] = d.x;
-                    acc[2 * k + 1] = d.y;
-                }
-        }
-        if (NORM) acc[2 * NV] += (y0.x * y0.x + y0.y * y0.y) + (y1.x * y1.x + y1.y * y1.y);
+        for (int k = 0; k < NV; k++)
+            if (k < nk) {
+                double2 d = make_double2(acc[2 * k], acc[2 * k + 1]);
+                cfmac(d, make_double2((double)v[k][0], (double)v[k][1]), y0);
+                cfmac(d, make_double2((double)v[k][2], (double)v[k][3]), y1);
+                acc[2 * k] = d.x;
+                acc[2 * k + 1] = d.y;
+            }
+        if (SUB) acc[2 * NV] += (y0.x * y0.x + y0.y * y0.y) + (y1.x * y1.x + y1.y * y1.y);
         if (e + G * PTPB * 2 < n) load(e + G * PTPB * 2);
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < NQ; q += 8)
-        if (q == 2 * NV ? NORM : DOTS && q < 2 * nk) {
+        if (q == 2 * NV ? SUB : q < 2 * nk) {
             const double s = wave_sum8(acc + q);
             if (!(lane & 7)) red[wave][q + (lane >> 3)] = s;
         }
     __syncthreads();
-    const int nq = (DOTS ? nk : 0) + (NORM ? 1 : 0);
+    const int nq = nk + (SUB ? 1 : 0);
     if ((int)threadIdx.x < nq) {
         const int q = threadIdx.x;
-        const bool norm = NORM && q == nq - 1;
+        const bool norm = SUB && q == nk;
         double re = 0, im = 0;
         for (int u = 0; u < PTPB / 64; u++) {
             re += red[u][norm ? 2 * NV : 2 * q];
@@ -520,19 +595,15 @@ __global__ __launch_bounds__(PTPB) void arnoldi_norm_kernel(int n, const float2 
     }
 }
 
-// the end of a cycle: nk coefficients of the last second pass (one right-hand
-// side) and the squared norm of the last vector, per segment
+// the end of a cycle: nk coefficients of the last second pass and the squared
+// norm of the last vector, per segment
 __global__ __launch_bounds__(256) void arnoldi_last_kernel(int nk, const double2 *__restrict__ pin, int npin,
                                                            double2 *__restrict__ h2, double2 *__restrict__ nr) {
     __shared__ double2 coef[NVMAX];
-    const int sg = blockIdx.x;
-    sum_quantities<4>(pin + (size_t)sg * npin, (size_t)npin, nk + 1, npin, coef);
-    if ((int)threadIdx.x < nk) h2[threadIdx.x] = coef[threadIdx.x];
-    if (threadIdx.x == 0) {
-        double nn = coef[nk].x;
-        for (int k = 0; k < nk; k++) nn -= coef[k].x * coef[k].x + coef[k].y * coef[k].y;
-        nr[sg] = make_double2(nn, 0);
-    }
+    const int sg = blockIdx.x, nb = gridDim.x;
+    sum_quantities<4>(pin + (size_t)sg * npin, (size_t)nb * npin, nk + 1, npin, coef);
+    if ((int)threadIdx.x < nk) h2[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
+    if (threadIdx.x == 0) nr[sg] = make_double2(rest_norm(coef, nk), 0);
 }
 
 int pass_grid(size_t n) {
@@ -541,7 +612,7 @@ int pass_grid(size_t n) {
 }
 
 size_t stream_lds(int n2, int j) {
-    const int NR = (n2 + 3) / 4, CG = STPB / NR;
+    const int NR = row_groups(n2), M = chain_length(n2), CG = (5 * NR + M - 1) / M;
     return 8 * ((size_t)(j + 2) * 5 * n2 + (size_t)CG * n2 + (size_t)4 * n2 * NR);
 }
 
@@ -577,42 +648,47 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
     void *work[2] = {work0, work1};
     const void *w = b;
     arnoldi_norm_kernel<<<grid, PTPB, 0, c->stream>>>((int)n, (const float2 *)b, part3);
-#define PASS_NV(NV, GA, SU, DO, NO, PIN, NPIN, POUT, HOUT)                                                        \
-    arnoldi_pass_kernel<NV, GA, SU, DO, NO><<<grid, PTPB, 0, c->stream>>>(Vc, n2, op.nbr, vl, j + 1, PIN, NPIN, y, t, \
-                                                                          POUT, HOUT)
-#define PASS(GA, SU, DO, NO, PIN, NPIN, POUT, HOUT)                              \
-    do {                                                                         \
-        if (j < 4) PASS_NV(4, GA, SU, DO, NO, PIN, NPIN, POUT, HOUT);            \
-        else if (j < 8) PASS_NV(8, GA, SU, DO, NO, PIN, NPIN, POUT, HOUT);       \
-        else if (j < 12) PASS_NV(12, GA, SU, DO, NO, PIN, NPIN, POUT, HOUT);     \
-        else PASS_NV(16, GA, SU, DO, NO, PIN, NPIN, POUT, HOUT);                 \
+#define PASS_NV(NV, SUB, PIN, NPIN, POUT, HOUT)                                                             \
+    arnoldi_pass_kernel<NV, SUB><<<grid, PTPB, 0, c->stream>>>(Vc, n2, op.nbr, vl, j + 1, PIN, NPIN, y, t, POUT, HOUT)
+#define PASS(SUB, PIN, NPIN, POUT, HOUT)                              \
+    do {                                                              \
+        if (j < 4) PASS_NV(4, SUB, PIN, NPIN, POUT, HOUT);            \
+        else if (j < 8) PASS_NV(8, SUB, PIN, NPIN, POUT, HOUT);       \
+        else if (j < 12) PASS_NV(12, SUB, PIN, NPIN, POUT, HOUT);     \
+        else PASS_NV(16, SUB, PIN, NPIN, POUT, HOUT);                 \
     } while (0)
     int rc = MGDD_OK;
     for (int j = 0; j < m && !rc; j++) {
         Basis vl{};
         for (int k = 0; k <= j; k++) vl.p[k] = (const float2 *)V[k];
         float2 *y = (float2 *)work[j & 1], *vj = (float2 *)V[j];
-        double2 *h1 = H1 + (size_t)j * (m + 1) * nb, *h2 = H2 + (size_t)j * (m + 1) * nb;
+        double2 *h1 = H1 + (size_t)j * (m + 1) * nb;
         // algorithmic bytes: the 5 blocks of every coarse site once per launch, per
         // right-hand side w read, y and v_j written and the j earlier basis vectors read
         const double abytes = (double)Vc * (5.0 * n2 * n2 * 8 + nb * (3.0 + j) * n2 * 8);
-        const int slot = kt_begin(c);
+        double2 *h2p = H2 + (size_t)(j ? j - 1 : 0) * (m + 1) * nb, *nrj = NR + (size_t)j * nb;
+        int slot;
         if (nb == 1) {
             const int gs = stream_grid(Vc, n2, j);
-            double2 *h2p = j ? H2 + (size_t)(j - 1) * (m + 1) : H2;
+            slot = kt_begin(c);
             arnoldi_stream_kernel<<<gs, STPB, stream_lds(n2, j), c->stream>>>(
-                Vc, N, op.nbr, H, (const float2 *)w, part3, G, vl, j, vj, y, t, part1, h2p, NR + j);
+                Vc, N, op.nbr, H, (const float2 *)w, part3, G, vl, j, vj, y, t, part1, h2p, nrj);
             kt_end(c, slot, KF_COARSE, MGDD_F32, (double)Vc, abytes);
-            PASS(true, true, true, true, part1, gs, part3, h1);
+            PASS(true, part1, gs, part3, h1);
         } else {
+#define VECTOR(NV)                                                                                                    \
+    arnoldi_vector_kernel<NV><<<grid, PTPB, 0, c->stream>>>((int)n, vl, j, part3, G, (const float2 *)w, vj, h2p, nrj)
+            if (j <= 4) VECTOR(4);
+            else if (j <= 8) VECTOR(8);
+            else VECTOR(16);
+#undef VECTOR
             const size_t lds = 8 * ((size_t)16 * mfma_ldx(n2) + (size_t)n2 * mfma_ldb(n2));
-            arnoldi_mfma_kernel<<<dim3(Vc, (nb + 15) / 16), 128 * ((n2 + 15) / 16), lds, c->stream>>>(
-                Vc, N, nb, op.nbr, H, (const float2 *)w, part3, G, vj, y, t, NR + (size_t)j * nb);
+            slot = kt_begin(c);
+            arnoldi_mfma_kernel<<<dim3(Vc, (nb + 15) / 16), 128 * ((n2 + 15) / 16), lds, c->stream>>>(Vc, N, nb, op.nbr,
+                                                                                                    H, vj, y, t);
             kt_end(c, slot, KF_COARSE, MGDD_F32, (double)Vc * nb, abytes);
-            PASS(true, false, true, false, nullptr, 0, part2, nullptr);
-            PASS(false, true, true, false, part2, G, part3, h1);
-            PASS(false, true, false, true, part3, G, part2, h2);
-            std::swap(part2, part3);   // the norms' partials are read from part3 next
+            PASS(false, nullptr, 0, part2, nullptr);
+            PASS(true, part2, G, part3, h1);
         }
         rc = hip_check(c, hipGetLastError(), "arnoldi");
         w = y;
@@ -620,7 +696,7 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
 #undef PASS
 #undef PASS_NV
     if (!rc) {
-        arnoldi_last_kernel<<<nb, 256, 0, c->stream>>>(nb == 1 ? m : 0, part3, G, H2 + (size_t)(m - 1) * (m + 1) * nb,
+        arnoldi_last_kernel<<<nb, 256, 0, c->stream>>>(m, part3, G, H2 + (size_t)(m - 1) * (m + 1) * nb,
                                                        NR + (size_t)m * nb);
         rc = hip_check(c, hipGetLastError(), "arnoldi");
     }
