@@ -202,101 +202,136 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(2))) void b
     }
 }
 
-// ---------------------------------------------------------------- restriction c = P^H f
+// ---------------------------------------------------------------- restriction c = P^H f, prolongation f = P c
 //
-// One workgroup per (aggregate, field). out[a * ostride + r * rstride + chi * N + k].
-// The workgroups of the nrhs fields of one aggregate are consecutive and on
-// one XCD, so the aggregate's columns of P come from HBM once per launch and
-// from L2 for the other fields. T: arithmetic and coarse precision; SP, SF:
-// storage of P and of the fine field (T, or half precision with T = float).
-template <typename T, typename SP = T, typename SF = T>
+// T: arithmetic and coarse precision; SP, SF: storage of P and of the fine
+// field (T, or half precision with T = float; the fine field rounded once to
+// nearest even). R right-hand sides per thread (where fewer exist the last one
+// is repeated and not written): a value of P is loaded once for all of them. A
+// thread holds one site and one chirality, 6 R complex values in registers, so
+// P is read once for up to 12 right-hand sides (FP64: 6); the next column's 6
+// values are loaded while one is used. The sums of a right-hand side do not
+// depend on R. Bound: reading P for one right-hand side (32^3 x 64, N = 24,
+// FP32: 862 and 983 us, 5.8 and 5.1 TB/s; 943 and 1007 us with both chiralities
+// in a thread), the vector units for many: 24^3 x 48, N = 24, 12 right-hand
+// sides in FP32: restriction 502 us (one workgroup per aggregate and
+// right-hand side: 1450 us), prolongation 472 us (one thread per site and
+// right-hand side: 1980 us).
+template <typename T, typename SP, typename SF, int R>
 __global__ __launch_bounds__(TPB) void restrict_kernel(int V, int Va, int N, const int *__restrict__ agg_sites,
-                                                       const C<SP> *__restrict__ P, const C<SF> *__restrict__ f,
-                                                       C<T> *__restrict__ out, size_t ostride, size_t rstride,
-                                                       int nrhs, int ks) {
+                                                             const C<SP> *__restrict__ P, const C<SF> *__restrict__ f,
+                                                             C<T> *__restrict__ out, int Vc, int nrhs, int ks) {
     extern __shared__ unsigned char smem[];
-    T *red = (T *)smem;  // [waves][N][4]
-    const int wg = xcd_block(gridDim.x);
-    // ks workgroups per (aggregate, field), each for a contiguous range of k
-    const int part = wg % ks, af = wg / ks;
-    const int a = af / nrhs, r = af % nrhs;
+    constexpr int NS = (2 * R + 7) / 8 * 8;   // sums per k, rounded up to eights
+    T *red = (T *)smem;                       // [waves][kper][NS]
+    const int wg = xcd_block(gridDim.x), r0 = blockIdx.y * R;
+    const int part = wg % ks, ac = wg / ks, chi = ac & 1, a = ac >> 1;
     const int kper = (N + ks - 1) / ks, kb = part * kper, ke = kb + kper < N ? kb + kper : N;
     const int *sites = agg_sites + (size_t)a * Va;
     const size_t fs = (size_t)12 * V;
-    const C<SF> *fr = f + (size_t)r * fs;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     auto wide = [](auto v) { return mk<T>((T)v.x, (T)v.y); };
-    // one site per thread when Va <= blockDim (the field values stay in registers)
-    C<T> f0[12];
-    const bool one = Va <= (int)blockDim.x;
-    if (one) {
-        int d = threadIdx.x < Va ? sites[threadIdx.x] : 0;
+    for (int l0 = 0; l0 < Va; l0 += blockDim.x) {
+        const int l = l0 + (int)threadIdx.x;
+        const bool active = l < Va;
+        const int d = sites[active ? l : Va - 1];
+        C<T> fv[R][6];
 #pragma unroll
-        for (int c = 0; c < 12; c++) f0[c] = threadIdx.x < Va ? wide(fr[(size_t)c * V + d]) : mk<T>(0, 0);
-    }
-    for (int k = kb; k < ke; k++) {
-        const C<SP> *pk = P + (size_t)k * fs;
-        T p0 = 0, p1 = 0, p2 = 0, p3 = 0;
-        for (int l = threadIdx.x; l < Va; l += blockDim.x) {
-            int d = sites[l];
+        for (int r = 0; r < R; r++) {
+            const C<SF> *fr = f + (size_t)(r0 + r < nrhs ? r0 + r : nrhs - 1) * fs + (size_t)6 * chi * V + d;
 #pragma unroll
-            for (int c = 0; c < 12; c++) {
-                C<T> pv = wide(pk[(size_t)c * V + d]), fv = one ? f0[c] : wide(fr[(size_t)c * V + d]);
-                T re = pv.x * fv.x + pv.y * fv.y, im = pv.x * fv.y - pv.y * fv.x;
-                if (c < 6) { p0 += re; p1 += im; } else { p2 += re; p3 += im; }
-            }
+            for (int c = 0; c < 6; c++) fv[r][c] = wide(fr[(size_t)c * V]);
         }
-        p0 = wsum(p0); p1 = wsum(p1); p2 = wsum(p2); p3 = wsum(p3);
-        if (lane == 0) {
-            T *o = red + ((size_t)w * N + k) * 4;
-            o[0] = p0; o[1] = p1; o[2] = p2; o[3] = p3;
+        const C<SP> *pk = P + (size_t)6 * chi * V + d;
+        C<SP> pn[6];
+#pragma unroll
+        for (int c = 0; c < 6; c++) pn[c] = pk[(size_t)kb * fs + (size_t)c * V];
+        for (int k = kb; k < ke; k++) {
+            C<T> pv[6];
+#pragma unroll
+            for (int c = 0; c < 6; c++) pv[c] = active ? wide(pn[c]) : mk<T>(0, 0);
+            const size_t kn = (size_t)(k + 1 < ke ? k + 1 : k) * fs;
+#pragma unroll
+            for (int c = 0; c < 6; c++) pn[c] = pk[kn + (size_t)c * V];
+            T s[NS];
+#pragma unroll
+            for (int q = 0; q < NS; q++) s[q] = 0;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                C<T> t = mk<T>(0, 0);
+#pragma unroll
+                for (int c = 0; c < 6; c++) cfmac(t, pv[c], fv[r][c]);
+                s[2 * r] = t.x;
+                s[2 * r + 1] = t.y;
+            }
+            T *o = red + ((size_t)w * kper + (k - kb)) * NS;
+#pragma unroll
+            for (int q = 0; q < NS; q += 8) {
+                const T v = wave_sum8(s + q);
+                if (!(lane & 7)) o[q + (lane >> 3)] = l0 ? o[q + (lane >> 3)] + v : v;
+            }
         }
     }
     __syncthreads();
-    const int nw = blockDim.x >> 6;
-    for (int i = threadIdx.x; i < 2 * N; i += blockDim.x) {
-        int chi = i / N, k = i % N;
-        if (k < kb || k >= ke) continue;
-        T re = 0, im = 0;
+    for (int i = threadIdx.x; i < (ke - kb) * R; i += blockDim.x) {
+        const int k = i % (ke - kb), r = i / (ke - kb);
+        if (r0 + r >= nrhs) break;
+        C<T> v = mk<T>(0, 0);
         for (int q = 0; q < nw; q++) {
-            re += red[((size_t)q * N + k) * 4 + 2 * chi];
-            im += red[((size_t)q * N + k) * 4 + 2 * chi + 1];
+            const T *o = red + ((size_t)q * kper + k) * NS + 2 * r;
+            v.x += o[0];
+            v.y += o[1];
         }
-        out[(size_t)a * ostride + (size_t)r * rstride + i] = mk<T>(re, im);
+        out[((size_t)(r0 + r) * Vc + a) * 2 * N + chi * N + kb + k] = v;
     }
 }
 
-// ---------------------------------------------------------------- prolongation f = P c
-//
-// One thread per (site, field), the fields of one site in consecutive threads:
-// they read the same entries of P, so P comes from HBM once per launch.
-// T: arithmetic and coarse precision; SP, SF: storage of P and of the fine
-// field (rounded once to nearest even when half precision).
-template <typename T, typename SP = T, typename SF = T>
+template <typename T, typename SP, typename SF, int R>
 __global__ __launch_bounds__(TPB) void prolong_kernel(int V, int Vc, int N, const int *__restrict__ site_agg,
-                                                      const C<SP> *__restrict__ P, const C<T> *__restrict__ cin,
-                                                      C<SF> *__restrict__ f, int nrhs) {
-    const size_t i = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (i >= (size_t)V * nrhs) return;
-    const int r = (int)(i % nrhs), d = (int)(i / nrhs);
-    const int a = site_agg[d];
-    const size_t fs = (size_t)12 * V;
-    const C<T> *x = cin + ((size_t)r * Vc + a) * 2 * N;
-    C<T> acc[12];
+                                                            const C<SP> *__restrict__ P, const C<T> *__restrict__ cin,
+                                                            C<SF> *__restrict__ f, int nrhs) {
+    const int wg = xcd_block(gridDim.x), chi = wg & 1, r0 = blockIdx.y * R;
+    const int i = (wg >> 1) * TPB + (int)threadIdx.x, d = i < V ? i : V - 1;
+    const int a = site_agg[d], au = __builtin_amdgcn_readfirstlane(a);
+    const size_t fs = (size_t)12 * V, xs = (size_t)Vc * 2 * N;
+    const C<SP> *pk = P + (size_t)6 * chi * V + d;
+    C<T> acc[R][6];
 #pragma unroll
-    for (int c = 0; c < 12; c++) acc[c] = mk<T>(0, 0);
-    for (int k = 0; k < N; k++) {
-        const C<SP> *pk = P + (size_t)k * fs;
-        C<T> x0 = x[k], x1 = x[N + k];
+    for (int r = 0; r < R; r++)
 #pragma unroll
-        for (int c = 0; c < 12; c++) {
-            const C<SP> pv = pk[(size_t)c * V + d];
-            cfma(acc[c], mk<T>((T)pv.x, (T)pv.y), c < 6 ? x0 : x1);
+        for (int c = 0; c < 6; c++) acc[r][c] = mk<T>(0, 0);
+    C<SP> pn[6];
+#pragma unroll
+    for (int c = 0; c < 6; c++) pn[c] = pk[(size_t)c * V];
+    // one aggregate per wave (aggregates that hold whole runs of 64 sites):
+    // the coarse values are wave-uniform and come through the scalar cache
+    auto columns = [&](int ax) {
+        const C<T> *x = cin + ((size_t)r0 * Vc + ax) * 2 * N + (size_t)chi * N;
+        for (int k = 0; k < N; k++) {
+            C<T> pv[6];
+#pragma unroll
+            for (int c = 0; c < 6; c++) pv[c] = mk<T>((T)pn[c].x, (T)pn[c].y);
+            const size_t kn = (size_t)(k + 1 < N ? k + 1 : k) * fs;
+#pragma unroll
+            for (int c = 0; c < 6; c++) pn[c] = pk[kn + (size_t)c * V];
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const C<T> xv = x[(size_t)(r0 + r < nrhs ? r : nrhs - 1 - r0) * xs + k];
+#pragma unroll
+                for (int c = 0; c < 6; c++) cfma(acc[r][c], pv[c], xv);
+            }
         }
-    }
-    C<SF> *fr = f + (size_t)r * fs;
+    };
+    if (__all(a == au)) columns(au);
+    else columns(a);
+    if (i >= V) return;
 #pragma unroll
-    for (int c = 0; c < 12; c++) fr[(size_t)c * V + d] = mk<SF>((SF)acc[c].x, (SF)acc[c].y);
+    for (int r = 0; r < R; r++) {
+        if (r0 + r >= nrhs) break;
+        C<SF> *fr = f + (size_t)(r0 + r) * fs + (size_t)6 * chi * V + d;
+#pragma unroll
+        for (int c = 0; c < 6; c++) fr[(size_t)c * V] = mk<SF>((SF)acc[r][c].x, (SF)acc[r][c].y);
+    }
 }
 
 // ---------------------------------------------------------------- coarse stencil y = D_c x
@@ -568,52 +603,69 @@ int launch_build_P(Ctx *c, const void *tv64) {
     return rc;
 }
 
-int launch_restrict_ex(Ctx *c, int prec, int nrhs, const void *P, const void *fine, void *out, size_t ostride,
-                       size_t rstride) {
-    const Level1 &L1 = c->c;
-    size_t lds = (size_t)(TPB / 64) * L1.N * 4 * (prec == MGDD_F64 ? 8 : 4);
-    // few (aggregate, field) pairs: split the test vectors over up to 4
-    // workgroups each, so that the launch fills the chip
-    int ks = 1;
-    while (ks < 4 && ks < L1.N && (size_t)L1.Vc * nrhs * ks < 1024) ks *= 2;
-    const unsigned grid = (unsigned)L1.Vc * (unsigned)nrhs * (unsigned)ks;
-    if (prec == MGDD_F64)
-        restrict_kernel<double><<<grid, TPB, lds, c->stream>>>(c->g.V, L1.Va, L1.N, L1.agg_sites, (const double2 *)P,
-                                                               (const double2 *)fine, (double2 *)out, ostride, rstride,
-                                                               nrhs, ks);
-    else if (prec == MGDD_F32)
-        restrict_kernel<float><<<grid, TPB, lds, c->stream>>>(c->g.V, L1.Va, L1.N, L1.agg_sites, (const float2 *)P,
-                                                              (const float2 *)fine, (float2 *)out, ostride, rstride,
-                                                              nrhs, ks);
-    else   // half-precision fine field and P, FP32 coarse field
-        restrict_kernel<float, _Float16, _Float16><<<grid, TPB, lds, c->stream>>>(
-            c->g.V, L1.Va, L1.N, L1.agg_sites, (const half_cx *)P, (const half_cx *)fine, (float2 *)out, ostride,
-            rstride, nrhs, ks);
-    return hip_check(c, hipGetLastError(), "restrict kernel");
+// right-hand sides per thread for nrhs of them: the registers hold 12 (FP64:
+// 6); the fewest that take them in the same number of groups
+static int rhs_per_thread(int prec, int nrhs) {
+    const int most = prec == MGDD_F64 ? 6 : 12, groups = (nrhs + most - 1) / most, need = (nrhs + groups - 1) / groups;
+    return need <= 2 ? need : need <= 4 ? 4 : need <= 6 ? 6 : need <= 8 ? 8 : 12;
 }
+
+#define MULTI_R(F, T, SP, SF)             \
+    do {                                  \
+        if (R == 1) F(T, SP, SF, 1);      \
+        else if (R == 2) F(T, SP, SF, 2); \
+        else if (R == 4) F(T, SP, SF, 4); \
+        else F(T, SP, SF, 6);             \
+    } while (0)
+#define MULTI_R12(F, T, SP, SF)            \
+    do {                                   \
+        if (R <= 6) MULTI_R(F, T, SP, SF); \
+        else if (R == 8) F(T, SP, SF, 8);  \
+        else F(T, SP, SF, 12);             \
+    } while (0)
+#define MULTI(F)                                                  \
+    do {                                                          \
+        if (prec == MGDD_F64) MULTI_R(F, double, double, double); \
+        else if (prec == MGDD_F32) MULTI_R12(F, float, float, float); \
+        else MULTI_R12(F, float, _Float16, _Float16);             \
+    } while (0)
 
 int launch_restrict(Ctx *c, int prec, int nrhs, const void *fine, void *coarse) {
     const Level1 &L1 = c->c;
-    size_t n2 = 2 * (size_t)L1.N;
-    return launch_restrict_ex(c, prec, nrhs, prec == MGDD_F64 ? L1.P64 : prec == MGDD_F32 ? L1.P32 : L1.P16, fine,
-                              coarse, n2, n2 * L1.Vc);
+    const void *P = prec == MGDD_F64 ? L1.P64 : prec == MGDD_F32 ? L1.P32 : L1.P16;
+    const int R = rhs_per_thread(prec, nrhs), groups = (nrhs + R - 1) / R;
+    // few (aggregate, chirality) pairs: split the test vectors over up to 4
+    // workgroups each, so that the launch fills the chip
+    int ks = 1;
+    while (ks < 4 && ks < L1.N && (size_t)L1.Vc * 2 * groups * ks < 1024) ks *= 2;
+    const int kper = (L1.N + ks - 1) / ks, ns = (2 * R + 7) / 8 * 8;
+    const unsigned threads = L1.Va >= TPB ? TPB : (unsigned)((L1.Va + 63) / 64 * 64);
+    const size_t lds = (size_t)(threads / 64) * kper * ns * (prec == MGDD_F64 ? 8 : 4);
+    const dim3 grid((unsigned)(L1.Vc * 2 * ks), (unsigned)groups);
+#define RESTRICT(T, SP, SF, RR)                                                                          \
+    restrict_kernel<T, SP, SF, RR><<<grid, threads, lds, c->stream>>>(                                   \
+        c->g.V, L1.Va, L1.N, L1.agg_sites, (const C<SP> *)P, (const C<SF> *)fine, (C<T> *)coarse, L1.Vc, nrhs, ks)
+    MULTI(RESTRICT);
+#undef RESTRICT
+    return hip_check(c, hipGetLastError(), "restrict kernel");
 }
 
 int launch_prolong(Ctx *c, int prec, int nrhs, const void *coarse, void *fine) {
     const Level1 &L1 = c->c;
-    size_t n = (size_t)c->g.V * nrhs;
-    unsigned nwg = (unsigned)((n + TPB - 1) / TPB);
-    if (prec == MGDD_F64)
-        prolong_kernel<double><<<nwg, TPB, 0, c->stream>>>(c->g.V, L1.Vc, L1.N, L1.site_agg, (const double2 *)L1.P64,
-                                                           (const double2 *)coarse, (double2 *)fine, nrhs);
-    else if (prec == MGDD_F32)
-        prolong_kernel<float><<<nwg, TPB, 0, c->stream>>>(c->g.V, L1.Vc, L1.N, L1.site_agg, (const float2 *)L1.P32,
-                                                          (const float2 *)coarse, (float2 *)fine, nrhs);
-    else   // FP32 coarse field, half-precision P and fine field
-        prolong_kernel<float, _Float16, _Float16><<<nwg, TPB, 0, c->stream>>>(
-            c->g.V, L1.Vc, L1.N, L1.site_agg, (const half_cx *)L1.P16, (const float2 *)coarse, (half_cx *)fine, nrhs);
+    const void *P = prec == MGDD_F64 ? L1.P64 : prec == MGDD_F32 ? L1.P32 : L1.P16;
+    const int R = rhs_per_thread(prec, nrhs);
+    const dim3 grid(2u * (unsigned)((c->g.V + TPB - 1) / TPB), (unsigned)((nrhs + R - 1) / R));
+#define PROLONG(T, SP, SF, RR)                                                                               \
+    prolong_kernel<T, SP, SF, RR><<<grid, TPB, 0, c->stream>>>(c->g.V, L1.Vc, L1.N, L1.site_agg,             \
+                                                               (const C<SP> *)P, (const C<T> *)coarse,       \
+                                                               (C<SF> *)fine, nrhs)
+    MULTI(PROLONG);
+#undef PROLONG
     return hip_check(c, hipGetLastError(), "prolong kernel");
 }
+#undef MULTI
+#undef MULTI_R12
+#undef MULTI_R
 
 int launch_stencil_apply(Ctx *c, const StencilOp &op, int prec, int nrhs, const void *in, void *out) {
     if (nrhs >= MFMA_MIN_RHS) {
