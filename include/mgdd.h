@@ -117,13 +117,14 @@ int mgdd_set_allocator(mgdd_ctx *ctx, mgdd_alloc_fn alloc, mgdd_free_fn free_fn,
  * Schwarz block shape (they change the schedule, never the arithmetic of a
  * site beyond the summation order of the FP32 Schwarz kernels):
  *   sap_lanes: lanes per site of the FP32 Schwarz colour kernel (Algorithm
- *     2.1): 0 automatic (2 when the links are special unitary and the
- *     staged links fit in LDS, else 4 when the staged links fit, else 1),
+ *     2.1): 0 automatic (special unitary links whose staged rows fit in
+ *     LDS: 2, or one lane with those rows staged on lattices of 262144
+ *     sites or more; else 4 when the staged links fit, else 1),
  *     1 (one lane per site, spinors in LDS), 2 (two lanes per site, one per
  *     chirality, rows 0 and 1 of the block's links staged in LDS; needs
  *     special unitary links) or 4 (four lanes per site, the whole links
- *     staged). Half-precision storage runs with 2 lanes only; FP64 sweeps
- *     always use 1.
+ *     staged). Half-precision storage runs with 0 or 2 only; FP64 sweeps
+ *     take no notice of it.
  *   dirac_stage: Wilson-clover apply with blocks of 256 sites: 0 automatic
  *     (the workgroup's block of spinors staged in LDS), 1 staged, -1 not
  *     staged (every neighbour read from memory).

@@ -6,6 +6,8 @@
 // the block dropped), block-wide dot products by wavefront butterflies plus
 // one LDS exchange, and finally z += e. Blocks of one colour never touch each
 // other, so all of them run at once.
+#include "lanes.h"
+#include "schwarz.h"
 #include "stencil.h"
 
 namespace mgdd {
@@ -14,44 +16,22 @@ namespace {
 
 template <typename T> struct Red3 { T a, b, c; };
 
-// v from lane (lane ^ X) of the same quad, X = 1 or 2: a DPP quad permutation
-// ([1,0,3,2] or [2,3,0,1]) for FP32, a cross-lane shuffle for FP64
-template <int X> __device__ inline float quad_xor(float v) {
-    constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xF, 0xF, false));
-}
-template <int X> __device__ inline double quad_xor(double v) { return __shfl_xor(v, X, 64); }
-
-// deterministic block-wide sum of three values: an XOR butterfly inside each
-// 64-lane wave (every lane ends with the same bits), then the per-wave sums
-// added in wave order by every thread.
+// deterministic block-wide sum of three values: lane permutations inside each
+// 64-lane wave, then the per-wave sums added in wave order by every thread.
 // TRAIL = false leaves out the closing barrier: for callers that pass a
-// barrier of their own before red is written again
+// barrier of their own before red (4 values a wave) is written again
 template <typename T, bool TRAIL = true> __device__ inline Red3<T> block_sum3(Red3<T> v, T *red) {
-#pragma unroll
-    for (int m = 32; m >= 4; m >>= 1) {
-        v.a += __shfl_xor(v.a, m, 64);
-        v.b += __shfl_xor(v.b, m, 64);
-        v.c += __shfl_xor(v.c, m, 64);
-    }
-    v.a += quad_xor<2>(v.a);
-    v.b += quad_xor<2>(v.b);
-    v.c += quad_xor<2>(v.c);
-    v.a += quad_xor<1>(v.a);
-    v.b += quad_xor<1>(v.b);
-    v.c += quad_xor<1>(v.c);
-    int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[3 * w] = v.a;
-        red[3 * w + 1] = v.b;
-        red[3 * w + 2] = v.c;
-    }
+    T t = swap_add<16>(swap_add<32>(v.a, v.b), swap_add<32>(v.c, v.c));   // rows of 16 lanes: a, c, b, c
+    t += dpp_mov<0x128>(t);
+    t = sum_of_8(t);
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    if (!(lane & 15)) red[(threadIdx.x >> 6) * 4 + (lane >> 4)] = t;
     __syncthreads();
     Red3<T> s{0, 0, 0};
     for (int i = 0; i < nw; i++) {
-        s.a += red[3 * i];
-        s.b += red[3 * i + 1];
-        s.c += red[3 * i + 2];
+        s.a += red[4 * i];
+        s.c += red[4 * i + 1];
+        s.b += red[4 * i + 2];
     }
     if (TRAIL) __syncthreads();
     return s;
@@ -75,7 +55,7 @@ __global__ __launch_bounds__(256) void sap_colour_kernel(Geom g, const C<T> *__r
     extern __shared__ unsigned char smem[];
     const int Vb = g.Vb;
     C<T> *rho_lds = (C<T> *)smem;                        // [12][Vb]
-    T *red = (T *)(smem + sizeof(C<T>) * 12 * Vb);      // [3 * waves]
+    T *red = (T *)(smem + sizeof(C<T>) * 12 * Vb);      // [4 * waves]
     const size_t V = g.V;
     const int pos = (colour ? g.ncol0 : 0) + xcd_block(gridDim.x);
     const int l = threadIdx.x;
@@ -291,7 +271,7 @@ template <typename T> __device__ inline void reduce_scatter4(const C<T> *acc, in
         for (int c = 0; c < 3; c++) {
             C<T> mine = hi ? acc[(2 + k) * 3 + c] : acc[k * 3 + c];
             C<T> send = hi ? acc[k * 3 + c] : acc[(2 + k) * 3 + c];
-            C<T> recv = mk<T>(quad_xor<2>(send.x), quad_xor<2>(send.y));
+            C<T> recv = mk<T>(dpp_mov<0x4E>(send.x), dpp_mov<0x4E>(send.y));
             kept[k][c] = cadd(mine, recv);
         }
     const bool odd = m & 1;
@@ -299,7 +279,7 @@ template <typename T> __device__ inline void reduce_scatter4(const C<T> *acc, in
     for (int c = 0; c < 3; c++) {
         C<T> mine = odd ? kept[1][c] : kept[0][c];
         C<T> send = odd ? kept[0][c] : kept[1][c];
-        C<T> recv = mk<T>(quad_xor<1>(send.x), quad_xor<1>(send.y));
+        C<T> recv = mk<T>(dpp_mov<0xB1>(send.x), dpp_mov<0xB1>(send.y));
         out[c] = cadd(mine, recv);
     }
 }
@@ -364,7 +344,7 @@ __global__ __launch_bounds__(1024) void sap4_kernel(Geom g, const C<T> *__restri
     const int RS = Vb + 4, MS = 9 * Vb + 4;
     C<T> *rho_lds = (C<T> *)smem;                        // [12][RS]
     C<T> *lnk_lds = rho_lds + 12 * RS;                   // [4][MS]: direction m, entry k at m MS + k Vb
-    T *red = (T *)(lnk_lds + 4 * MS);                    // [3 * waves]
+    T *red = (T *)(lnk_lds + 4 * MS);                    // [4 * waves]
     const size_t V = g.V;
     const int pos = (colour ? g.ncol0 : 0) + xcd_block(gridDim.x);
     const int m = threadIdx.x & 3, l = threadIdx.x >> 2;
@@ -543,19 +523,19 @@ __global__ __launch_bounds__(1024) void sap4_kernel(Geom g, const C<T> *__restri
 // h = (1 -+ gamma) psi projected to its upper half (FWD: 1 - gamma) for the
 // lane's first (FIRST) or second direction; u: upper spins of psi, la / lb:
 // the lower spins l_pi(0), l_pi(1)
-template <bool FIRST, bool FWD>
-__device__ inline void project2(const float2 *u, const float2 *la, const float2 *lb, float sig, float2 *h) {
+template <typename T, bool FIRST, bool FWD>
+__device__ inline void project2(const C<T> *u, const C<T> *la, const C<T> *lb, T sig, C<T> *h) {
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-        const float2 u0 = u[a], u1 = u[3 + a], p = la[a], q = lb[a];
+        const C<T> u0 = u[a], u1 = u[3 + a], p = la[a], q = lb[a];
         if (FIRST) {          // beta l = (-i l_a, -i sig l_b)
-            h[a] = FWD ? make_float2(u0.x - p.y, u0.y + p.x) : make_float2(u0.x + p.y, u0.y - p.x);
-            h[3 + a] = FWD ? make_float2(fmaf(-sig, q.y, u1.x), fmaf(sig, q.x, u1.y))
-                           : make_float2(fmaf(sig, q.y, u1.x), fmaf(-sig, q.x, u1.y));
+            h[a] = FWD ? mk<T>(u0.x - p.y, u0.y + p.x) : mk<T>(u0.x + p.y, u0.y - p.x);
+            h[3 + a] = FWD ? mk<T>(fma(-sig, q.y, u1.x), fma(sig, q.x, u1.y))
+                           : mk<T>(fma(sig, q.y, u1.x), fma(-sig, q.x, u1.y));
         } else {              // beta l = (-l_a, sig l_b)
-            h[a] = FWD ? make_float2(u0.x + p.x, u0.y + p.y) : make_float2(u0.x - p.x, u0.y - p.y);
-            h[3 + a] = FWD ? make_float2(fmaf(-sig, q.x, u1.x), fmaf(-sig, q.y, u1.y))
-                           : make_float2(fmaf(sig, q.x, u1.x), fmaf(sig, q.y, u1.y));
+            h[a] = FWD ? mk<T>(u0.x + p.x, u0.y + p.y) : mk<T>(u0.x - p.x, u0.y - p.y);
+            h[3 + a] = FWD ? mk<T>(fma(-sig, q.x, u1.x), fma(-sig, q.y, u1.y))
+                           : mk<T>(fma(sig, q.x, u1.x), fma(sig, q.y, u1.y));
         }
     }
 }
@@ -563,35 +543,35 @@ __device__ inline void project2(const float2 *u, const float2 *la, const float2 
 // w = U h (FWD) or U^H h on the two colour vectors of h, then up += w and
 // L_t -+= conj(beta_t) w_t (the lower spins, kept in pi order: lower spin s
 // receives L_pi(s)); forward hops subtract, backward hops add
-template <bool FIRST, bool FWD>
-__device__ inline void accumulate_hop(const float2 *u, const float2 *h, float sig, float2 *up, float2 *L) {
-    float2 w[6];
-    su3_mv<float, !FWD>(u, h, w);
-    su3_mv<float, !FWD>(u, h + 3, w + 3);
+template <typename T, bool FIRST, bool FWD>
+__device__ inline void accumulate_hop(const C<T> *u, const C<T> *h, T sig, C<T> *up, C<T> *L) {
+    C<T> w[6];
+    su3_mv<T, !FWD>(u, h, w);
+    su3_mv<T, !FWD>(u, h + 3, w + 3);
 #pragma unroll
     for (int a = 0; a < 6; a++) up[a] = cadd(up[a], w[a]);
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-        const float2 w0 = w[a], w1 = w[3 + a];
+        const C<T> w0 = w[a], w1 = w[3 + a];
         // FIRST: conj(beta) = (i, i sig); second: (-1, sig)
-        const float2 c0 = FIRST ? make_float2(-w0.y, w0.x) : make_float2(-w0.x, -w0.y);
-        const float2 c1 = FIRST ? make_float2(-sig * w1.y, sig * w1.x) : make_float2(sig * w1.x, sig * w1.y);
+        const C<T> c0 = FIRST ? mk<T>(-w0.y, w0.x) : mk<T>(-w0.x, -w0.y);
+        const C<T> c1 = FIRST ? mk<T>(-sig * w1.y, sig * w1.x) : mk<T>(sig * w1.x, sig * w1.y);
         L[a] = FWD ? csub(L[a], c0) : cadd(L[a], c0);
         L[3 + a] = FWD ? csub(L[3 + a], c1) : cadd(L[3 + a], c1);
     }
 }
 
 // rows 0 and 1 of a link from LDS ([6][LS] entries of its direction), row 2 rebuilt
-template <int LS> __device__ inline void link_from_lds(const float2 *lk, int site, float sign, float2 *u) {
+template <typename T, int LS> __device__ inline void link_from_lds(const C<T> *lk, int site, T sign, C<T> *u) {
 #pragma unroll
     for (int k = 0; k < 6; k++) u[k] = lk[k * LS + site];
-    su3_row2<float>(u, sign);
+    su3_row2<T>(u, sign);
 }
 
 // the spinor at `site` of a field in LDS ([12][RS]): upper spins, and the
 // lower spins in pi order (component blocks src0, src1 chosen per lane)
-template <int RS>
-__device__ inline void spinor_from_lds(const float2 *rl, int site, int src0, int src1, float2 *u, float2 *la, float2 *lb) {
+template <typename T, int RS>
+__device__ inline void spinor_from_lds(const C<T> *rl, int site, int src0, int src1, C<T> *u, C<T> *la, C<T> *lb) {
 #pragma unroll
     for (int c = 0; c < 6; c++) u[c] = rl[c * RS + site];
 #pragma unroll
@@ -602,9 +582,9 @@ __device__ inline void spinor_from_lds(const float2 *rl, int site, int src0, int
 }
 
 // the same from a field in memory (device site dn; FV: FP32 or half storage)
-template <typename FV>
-__device__ inline void spinor_from_field(const FV &f, int dn, int src0, int src1, float2 *u, float2 *la,
-                                         float2 *lb) {
+template <typename T, typename FV>
+__device__ inline void spinor_from_field(const FV &f, int dn, int src0, int src1, C<T> *u, C<T> *la,
+                                         C<T> *lb) {
 #pragma unroll
     for (int c = 0; c < 6; c++) u[c] = f.ld(c, dn);
     // src0, src1 in {6, 9}: the lane's choice enters through the vector offset
@@ -617,83 +597,108 @@ __device__ inline void spinor_from_field(const FV &f, int dn, int src0, int src1
 
 // c ? a : b on values (a select of two array elements' addresses would keep
 // the arrays in scratch memory)
-__device__ inline float2 sel2(bool c, float2 a, float2 b) { return make_float2(c ? a.x : b.x, c ? a.y : b.y); }
+template <typename V> __device__ inline V sel2(bool c, V a, V b) {
+    V v;
+    v.x = c ? a.x : b.x;
+    v.y = c ? a.y : b.y;
+    return v;
+}
 
 // the lane's chirality of the hop sum: lane 0 keeps the upper spins and sends
 // its lower sums (kept in swapped order) to lane 1; lane 1 keeps the lower
 // spins and sends its upper sums
-__device__ inline void exchange_chirality(bool h, const float2 *up, const float2 *L, float2 *hs) {
+template <typename T>
+__device__ inline void exchange_chirality(bool h, const C<T> *up, const C<T> *L, C<T> *hs) {
 #pragma unroll
     for (int k = 0; k < 6; k++) {
         const int kp = k < 3 ? k + 3 : k - 3;
-        const float2 send = sel2(h, up[k], L[kp]);
-        const float2 mine = sel2(h, L[k], up[k]);
-        hs[k] = make_float2(mine.x + quad_xor<1>(send.x), mine.y + quad_xor<1>(send.y));
+        const C<T> send = sel2(h, up[k], L[kp]);
+        const C<T> mine = sel2(h, L[k], up[k]);
+        hs[k] = mk<T>(mine.x + dpp_mov<0xB1>(send.x), mine.y + dpp_mov<0xB1>(send.y));
     }
 }
 
 // the lane's hops whose neighbour lies in the block: the neighbour's spinor
 // from the LDS field fl ([12][RS]), links from LDS (rows 0 and 1 of each
 // site's forward links, [4][6][LS]); up / L accumulate as in accumulate_hop
-template <int RS, int LS>
-__device__ inline void block_hops(const float2 *fl, const float2 *lnk, int h, int l, const int *lnf, const int *lnb,
-                                  int src0, int src1, float sig, float sgf, float sgb, float2 *up, float2 *L) {
+template <typename T, int RS, int LS>
+__device__ inline void block_hops(const C<T> *fl, const C<T> *lnk, int h, int l, const int *lnf, const int *lnb,
+                                  int src0, int src1, T sig, T sgf, T sgb, C<T> *up, C<T> *L) {
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-        const float2 *lk = lnk + (2 * h + i) * 6 * LS;
-        const float sf = i ? sgf : 1.f, sb = i ? sgb : 1.f;
-        float2 u[9], ps[6], la[3], lb[3], hh[6];
+        const C<T> *lk = lnk + (2 * h + i) * 6 * LS;
+        const T sf = i ? sgf : (T)1, sb = i ? sgb : (T)1;
+        C<T> u[9], ps[6], la[3], lb[3], hh[6];
         if (lnf[i] >= 0) {
-            spinor_from_lds<RS>(fl, lnf[i], src0, src1, ps, la, lb);
-            link_from_lds<LS>(lk, l, sf, u);
+            spinor_from_lds<T, RS>(fl, lnf[i], src0, src1, ps, la, lb);
+            link_from_lds<T, LS>(lk, l, sf, u);
             if (i == 0) {
-                project2<true, true>(ps, la, lb, sig, hh);
-                accumulate_hop<true, true>(u, hh, sig, up, L);
+                project2<T, true, true>(ps, la, lb, sig, hh);
+                accumulate_hop<T, true, true>(u, hh, sig, up, L);
             } else {
-                project2<false, true>(ps, la, lb, sig, hh);
-                accumulate_hop<false, true>(u, hh, sig, up, L);
+                project2<T, false, true>(ps, la, lb, sig, hh);
+                accumulate_hop<T, false, true>(u, hh, sig, up, L);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
         if (lnb[i] >= 0) {
-            spinor_from_lds<RS>(fl, lnb[i], src0, src1, ps, la, lb);
-            link_from_lds<LS>(lk, lnb[i], sb, u);
+            spinor_from_lds<T, RS>(fl, lnb[i], src0, src1, ps, la, lb);
+            link_from_lds<T, LS>(lk, lnb[i], sb, u);
             if (i == 0) {
-                project2<true, false>(ps, la, lb, sig, hh);
-                accumulate_hop<true, false>(u, hh, sig, up, L);
+                project2<T, true, false>(ps, la, lb, sig, hh);
+                accumulate_hop<T, true, false>(u, hh, sig, up, L);
             } else {
-                project2<false, false>(ps, la, lb, sig, hh);
-                accumulate_hop<false, false>(u, hh, sig, up, L);
+                project2<T, false, false>(ps, la, lb, sig, hh);
+                accumulate_hop<T, false, false>(u, hh, sig, up, L);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// S: storage of the spinor fields b and z (float, or _Float16: half-precision
-// storage with the same FP32 arithmetic, z rounded once when it is stored)
-template <int VB, typename S = float>
-__global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) void sapc_kernel(
-    Geom g, const float2 *__restrict__ Up, const float2 *__restrict__ Ap, const void *__restrict__ b,
-    void *__restrict__ z, int colour, int mr, float sre, float sim, int antiperiodic) {
-    using FV = typename F32Store<S>::view;
+// NC consecutive components from component `first` (lane-dependent) on of an
+// array of 36 per site: FP32 through one descriptor of the whole array, the
+// lane's choice in the 32-bit offset; FP64 arrays of that many components pass
+// the descriptor's 4 GB, so through a lane's own pointer
+template <typename T> struct LaneBlock;
+template <> struct LaneBlock<float> {
+    FieldView<float> f;
+    unsigned off;
+    __device__ LaneBlock(const float2 *p, size_t V, int first) : f(p, V, 36), off((unsigned)first * f.cs) {}
+    template <bool NT = false> __device__ float2 ld(int k, int site, unsigned salt = 0) const {
+        return f.template ld_lane<NT>(k, site, off, salt);
+    }
+};
+template <> struct LaneBlock<double> {
+    const double2 *p;
+    size_t V;
+    __device__ LaneBlock(const double2 *q, size_t v, int first) : p(q + (size_t)first * v), V(v) {}
+    template <bool NT = false> __device__ double2 ld(int k, int site, unsigned salt = 0) const {
+        return p[(size_t)k * V + (unsigned)site + salt];
+    }
+};
+
+template <typename T, int VB, typename FV, int ESZ>
+__device__ inline void sapc_step(const Geom &g, const C<T> *__restrict__ Up, const C<T> *__restrict__ Ap,
+                                 const void *__restrict__ b, void *__restrict__ z, int colour, int mr, T sre, T sim,
+                                 int antiperiodic) {
     extern __shared__ unsigned char smem[];
-    constexpr int Vb = VB, RS = VB + 4, LS = VB + 2;
-    float2 *rho_lds = (float2 *)smem;                   // [12][RS]
-    float2 *lnk = rho_lds + 12 * RS;                    // [4][6][LS]: rows 0, 1 of each site's forward links
-    float *red = (float *)(lnk + 24 * LS);              // [3 * waves]
+    constexpr int RS = VB + 4, LS = VB + 2;
+    C<T> *rho_lds = (C<T> *)smem;                   // [12][RS]
+    C<T> *lnk = rho_lds + 12 * RS;                    // [4][6][LS]: rows 0, 1 of each site's forward links
+    T *red = (T *)(lnk + 24 * LS);              // [4 * waves]
     const size_t V = g.V;
     const int pos = (colour ? g.ncol0 : 0) + xcd_block(gridDim.x);
     const int h = threadIdx.x & 1, l = threadIdx.x >> 1;
     const int d = (pos << g.lgVb) + l;
-    const size_t roff = (size_t)blockIdx.y * 12 * V * F32Store<S>::ESZ;   // bytes
-    const FieldView<float> Uall(Up, V, 36), Aall(Ap, V, 36);
-    const FV bf((const float2 *)((const char *)b + roff), V, 12), zf((const float2 *)((const char *)z + roff), V, 12);
-    const unsigned aoff = (unsigned)h * 18u * Aall.cs, coff = (unsigned)h * 6u * zf.cs;
+    const size_t roff = (size_t)blockIdx.y * 12 * V * ESZ;   // bytes
+    const LaneBlock<T> U0(Up, V, 18 * h), U1(Up, V, 18 * h + 9), A(Ap, V, 18 * h);   // directions 2h, 2h + 1; chirality h
+    const FV bf((const C<T> *)((const char *)b + roff), V, 12), zf((const C<T> *)((const char *)z + roff), V, 12);
+    const unsigned coff = (unsigned)h * 6u * zf.cs;
     const bool swp = h == 0;
-    const float sig = h ? -1.f : 1.f;
+    const T sig = h ? (T)-1 : (T)1;
     const int src0 = swp ? 9 : 6, src1 = swp ? 6 : 9;   // LDS component blocks of l_pi(0), l_pi(1)
-    const float2 shift = make_float2(sre, sim);
+    const C<T> shift = mk<T>(sre, sim);
 
     // neighbours along the lane's two directions mu = 2h + i (every private
     // array index a compile-time constant)
@@ -727,11 +732,11 @@ __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
     // signs of the rebuilt time links (second direction of lane 1): -1 on the
     // link across the antiperiodic time boundary
-    float sgf = 1.f, sgb = 1.f;
+    T sgf = (T)1, sgb = (T)1;
     {
         const int t = (int)((g.blk_coord[pos] >> 24) << g.lb[3]) + x[3];
-        if (antiperiodic && h == 1 && t == g.L[3] - 1) sgf = -1.f;
-        if (antiperiodic && h == 1 && t == 0) sgb = -1.f;
+        if (antiperiodic && h == 1 && t == g.L[3] - 1) sgf = (T)-1;
+        if (antiperiodic && h == 1 && t == 0) sgb = (T)-1;
     }
 
     // stage rows 0 and 1 of the site's forward links of the lane's
@@ -741,10 +746,10 @@ __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) voi
     // step reads again, stay in L2 (20 % fewer bytes from memory)
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-        const unsigned uo = (unsigned)(2 * h + i) * 9u * Uall.cs;
-        float2 *lk = lnk + (2 * h + i) * 6 * LS;
+        const LaneBlock<T> &Ui = i ? U1 : U0;
+        C<T> *lk = lnk + (2 * h + i) * 6 * LS;
 #pragma unroll
-        for (int k = 0; k < 6; k++) lk[k * LS + l] = Uall.template ld_lane<true>(k, d, uo);
+        for (int k = 0; k < 6; k++) lk[k * LS + l] = Ui.template ld<true>(k, d);
     }
 #pragma unroll
     for (int c = 0; c < 6; c++) rho_lds[(6 * h + c) * RS + l] = zf.template ld_lane<true>(c, d, coff);
@@ -753,61 +758,61 @@ __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) voi
     // r = b - (D - shift) z on the lane's chirality: the hops inside the
     // block from LDS, then those that leave it (spinor and, backward, link
     // from memory)
-    float2 rho[6], e[6];
+    C<T> rho[6], e[6];
     {
         // half of the clover rows before the hops, as in the MR steps below
-        float2 ap0[18];
+        C<T> ap0[18];
 #pragma unroll
-        for (int k = 0; k < 9; k++) ap0[k] = Aall.ld_lane(k, d, aoff);
-        float2 up[6], L[6];
+        for (int k = 0; k < 9; k++) ap0[k] = A.ld(k, d);
+        C<T> up[6], L[6];
 #pragma unroll
-        for (int k = 0; k < 6; k++) up[k] = L[k] = make_float2(0.f, 0.f);
-        block_hops<RS, LS>(rho_lds, lnk, h, l, lnf, lnb, src0, src1, sig, sgf, sgb, up, L);
+        for (int k = 0; k < 6; k++) up[k] = L[k] = mk<T>((T)0, (T)0);
+        block_hops<T, RS, LS>(rho_lds, lnk, h, l, lnf, lnb, src0, src1, sig, sgf, sgb, up, L);
 #pragma unroll
         for (int i = 0; i < 2; i++) {
-            const float sf = i ? sgf : 1.f, sb = i ? sgb : 1.f;
-            float2 u[9], ps[6], la[3], lb[3], hh[6];
+            const T sf = i ? sgf : (T)1, sb = i ? sgb : (T)1;
+            const LaneBlock<T> &Ui = i ? U1 : U0;
+            C<T> u[9], ps[6], la[3], lb[3], hh[6];
             if (lnf[i] < 0) {
-                spinor_from_field(zf, nf[i], src0, src1, ps, la, lb);
-                link_from_lds<LS>(lnk + (2 * h + i) * 6 * LS, l, sf, u);
+                spinor_from_field<T>(zf, nf[i], src0, src1, ps, la, lb);
+                link_from_lds<T, LS>(lnk + (2 * h + i) * 6 * LS, l, sf, u);
                 if (i == 0) {
-                    project2<true, true>(ps, la, lb, sig, hh);
-                    accumulate_hop<true, true>(u, hh, sig, up, L);
+                    project2<T, true, true>(ps, la, lb, sig, hh);
+                    accumulate_hop<T, true, true>(u, hh, sig, up, L);
                 } else {
-                    project2<false, true>(ps, la, lb, sig, hh);
-                    accumulate_hop<false, true>(u, hh, sig, up, L);
+                    project2<T, false, true>(ps, la, lb, sig, hh);
+                    accumulate_hop<T, false, true>(u, hh, sig, up, L);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
             if (lnb[i] < 0) {
-                spinor_from_field(zf, nbk[i], src0, src1, ps, la, lb);
-                const unsigned uo = (unsigned)(2 * h + i) * 9u * Uall.cs;
+                spinor_from_field<T>(zf, nbk[i], src0, src1, ps, la, lb);
 #pragma unroll
-                for (int k = 0; k < 6; k++) u[k] = Uall.ld_lane(k, nbk[i], uo);
-                su3_row2<float>(u, sb);
+                for (int k = 0; k < 6; k++) u[k] = Ui.ld(k, nbk[i]);
+                su3_row2<T>(u, sb);
                 if (i == 0) {
-                    project2<true, false>(ps, la, lb, sig, hh);
-                    accumulate_hop<true, false>(u, hh, sig, up, L);
+                    project2<T, true, false>(ps, la, lb, sig, hh);
+                    accumulate_hop<T, true, false>(u, hh, sig, up, L);
                 } else {
-                    project2<false, false>(ps, la, lb, sig, hh);
-                    accumulate_hop<false, false>(u, hh, sig, up, L);
+                    project2<T, false, false>(ps, la, lb, sig, hh);
+                    accumulate_hop<T, false, false>(u, hh, sig, up, L);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        float2 hs[6], zc[6], az[6];
-        exchange_chirality(h, up, L, hs);
+        C<T> hs[6], zc[6], az[6];
+        exchange_chirality<T>(h, up, L, hs);
 #pragma unroll
         for (int c = 0; c < 6; c++) zc[c] = rho_lds[(6 * h + c) * RS + l];
 #pragma unroll
-        for (int k = 9; k < 18; k++) ap0[k] = Aall.ld_lane(k, d, aoff);
-        herm6_mv<float>(ap0, zc, az);
+        for (int k = 9; k < 18; k++) ap0[k] = A.ld(k, d);
+        herm6_mv<T>(ap0, zc, az);
 #pragma unroll
         for (int c = 0; c < 6; c++) {
-            const float2 bs = bf.template ld_lane<true>(c, d, coff);
-            const float2 dz = csub(csub(az[c], cscale(hs[c], 0.5f)), cmul(shift, zc[c]));
+            const C<T> bs = bf.template ld_lane<true>(c, d, coff);
+            const C<T> dz = csub(csub(az[c], cscale(hs[c], (T)0.5)), cmul(shift, zc[c]));
             rho[c] = csub(bs, dz);
-            e[c] = make_float2(0.f, 0.f);
+            e[c] = mk<T>((T)0, (T)0);
         }
     }
     // every lane has read z from LDS before rho replaces it
@@ -818,34 +823,34 @@ __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) voi
 
     for (int it = 0; it < mr; it++) {
         const unsigned salt = opaque_zero();
-        float2 up[6], L[6];
+        C<T> up[6], L[6];
 #pragma unroll
-        for (int k = 0; k < 6; k++) up[k] = L[k] = make_float2(0.f, 0.f);
+        for (int k = 0; k < 6; k++) up[k] = L[k] = mk<T>((T)0, (T)0);
         // half of the clover rows (from L2) are loaded before the hops,
         // which hide their latency (all 18 would not fit the registers)
-        float2 ap[18];
+        C<T> ap[18];
 #pragma unroll
-        for (int k = 0; k < 9; k++) ap[k] = Aall.ld_lane(k, d, aoff, salt);
-        block_hops<RS, LS>(rho_lds, lnk, h, l, lnf, lnb, src0, src1, sig, sgf, sgb, up, L);
-        float2 hs[6], ax[6], q[6];
-        exchange_chirality(h, up, L, hs);
+        for (int k = 0; k < 9; k++) ap[k] = A.template ld<false>(k, d, salt);
+        block_hops<T, RS, LS>(rho_lds, lnk, h, l, lnf, lnb, src0, src1, sig, sgf, sgb, up, L);
+        C<T> hs[6], ax[6], q[6];
+        exchange_chirality<T>(h, up, L, hs);
 #pragma unroll
-        for (int k = 9; k < 18; k++) ap[k] = Aall.ld_lane(k, d, aoff, salt);
-        herm6_mv<float>(ap, rho, ax);
-        Red3<float> part{0, 0, 0};
+        for (int k = 9; k < 18; k++) ap[k] = A.template ld<false>(k, d, salt);
+        herm6_mv<T>(ap, rho, ax);
+        Red3<T> part{0, 0, 0};
 #pragma unroll
         for (int c = 0; c < 6; c++) {
-            q[c] = csub(csub(ax[c], cscale(hs[c], 0.5f)), cmul(shift, rho[c]));
+            q[c] = csub(csub(ax[c], cscale(hs[c], (T)0.5)), cmul(shift, rho[c]));
             part.a += q[c].x * q[c].x + q[c].y * q[c].y;
             part.b += q[c].x * rho[c].x + q[c].y * rho[c].y;   // conj(q) rho
             part.c += q[c].x * rho[c].y - q[c].y * rho[c].x;
         }
         // the barrier after the rho update below (or the end of the loop) comes
         // before any thread writes red again
-        Red3<float> sm = block_sum3<float, false>(part, red);
-        if (sm.a == 0.f) break;
-        const float inv = 1.f / sm.a;
-        const float2 alpha = make_float2(sm.b * inv, sm.c * inv);
+        Red3<T> sm = block_sum3<T, false>(part, red);
+        if (sm.a == (T)0) break;
+        const T inv = (T)1 / sm.a;
+        const C<T> alpha = mk<T>(sm.b * inv, sm.c * inv);
 #pragma unroll
         for (int c = 0; c < 6; c++) {
             cfma(e[c], alpha, rho[c]);
@@ -862,6 +867,21 @@ __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) voi
         zf.template st_lane<true>(c, d, coff, cadd(zf.template ld_lane<true>(c, d, coff), e[c]));
 }
 
+template <int VB, typename S>
+__global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) void sapc_kernel(
+    Geom g, const float2 *__restrict__ Up, const float2 *__restrict__ Ap, const void *__restrict__ b,
+    void *__restrict__ z, int colour, int mr, float sre, float sim, int antiperiodic) {
+    sapc_step<float, VB, typename F32Store<S>::view, (int)F32Store<S>::ESZ>(g, Up, Ap, b, z, colour, mr, sre, sim,
+                                                                           antiperiodic);
+}
+
+template <int VB>
+__global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(2))) void sapc64_kernel(
+    Geom g, const double2 *__restrict__ Up, const double2 *__restrict__ Ap, const void *__restrict__ b,
+    void *__restrict__ z, int colour, int mr, double sre, double sim, int antiperiodic) {
+    sapc_step<double, VB, FieldView<double>, 16>(g, Up, Ap, b, z, colour, mr, sre, sim, antiperiodic);
+}
+
 }  // namespace
 
 int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, double sim, const void *b, void *z) {
@@ -870,11 +890,11 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
         return fail(c, MGDD_ESHAPE, "the Schwarz kernel needs a block volume of 64, 128 or 256");
     const int nblocks = col ? g.nblocks - g.ncol0 : g.ncol0;
     if (nblocks == 0) return MGDD_OK;
-    size_t lds = (prec == MGDD_F64 ? 16 : 8) * 12 * (size_t)g.Vb + (prec == MGDD_F64 ? 8 : 4) * 3 * (g.Vb / 64);
+    size_t lds = (prec == MGDD_F64 ? 16 : 8) * 12 * (size_t)g.Vb + (prec == MGDD_F64 ? 8 : 4) * 4 * (g.Vb / 64);
     // four lanes per site with the block's links staged in LDS (FP32)
-    const size_t lds4 = 8 * (12 * ((size_t)g.Vb + 4) + 4 * (9 * (size_t)g.Vb + 4)) + 4 * 3 * (4 * g.Vb / 64);
+    const size_t lds4 = 8 * (12 * ((size_t)g.Vb + 4) + 4 * (9 * (size_t)g.Vb + 4)) + 4 * 4 * (4 * g.Vb / 64);
     // two lanes per site, the links' first two rows staged (special unitary links)
-    const size_t ldsc = 8 * (12 * ((size_t)g.Vb + 4) + 24 * ((size_t)g.Vb + 2)) + 4 * 3 * (2 * g.Vb / 64);
+    const size_t ldsc = 8 * (12 * ((size_t)g.Vb + 4) + 24 * ((size_t)g.Vb + 2)) + 4 * 4 * (2 * g.Vb / 64);
     dim3 grid(nblocks, nrhs);
     const bool two_ok = c->links_su3 && ldsc <= c->lds_max, four_ok = lds4 <= c->lds_max;
     // lanes per site of the FP32 kernels: the context's choice, else automatic
@@ -888,8 +908,25 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
                     lanes == 2 ? "the two-lanes-per-site Schwarz kernel needs special unitary links and the block's "
                                  "link rows in LDS"
                                : "the four-lanes-per-site Schwarz kernel needs the block's links in LDS");
+    // Special unitary links in FP32 and half storage: one lane per site needs
+    // fewer instructions, two lanes give twice the waves. A colour of 131072
+    // sites is two waves of one-lane sites per SIMD, all that fit, and from
+    // there on one lane is faster (one sweep, 4 MR steps, FP32, one / two
+    // lanes: 16^3 x 32 73 / 67 us, 16^2 x 32^2 100 / 107, 24^3 x 48 260 / 279,
+    // 32^3 x 64 653 / 772; 4^3 x 2 and 2^2 x 4^2 blocks cross at the same
+    // size). The number of right-hand sides does not enter: one of them gets
+    // the same result alone and among others.
+    const bool site = prec != MGDD_F64 && c->sap_lanes == 0 && lanes == 2 && g.V >= 262144 &&
+                      sap_site_lds(g.Vb) <= c->lds_max;
+    // FP64: the two-lane kernel where its LDS fits (12 x 20 x 16 x 24 with 2^2
+    // x 4^2 blocks, 3 right-hand sides, one colour: 101 us against 158 with
+    // one lane per site and the links read from memory in every MR step)
+    const bool two64 = prec == MGDD_F64 && c->links_su3 && 2 * ldsc <= c->lds_max;
     const int slot = kt_begin(c);
-    if ((prec == MGDD_F32 || prec == MGDD_F16) && lanes == 2) {
+    int rc = MGDD_OK;
+    if (site) {
+        rc = launch_sap_site(c, prec, nrhs, col, mr, sre, sim, b, z);
+    } else if ((prec == MGDD_F32 || prec == MGDD_F16) && lanes == 2) {
         const int anti = c->t_antiperiodic ? 1 : 0;
 #define SAPC(VB, S)                                                                                               \
     sapc_kernel<VB, S><<<grid, 2 * VB, ldsc, c->stream>>>(g, (const float2 *)c->U32, (const float2 *)c->A32, b, z, \
@@ -904,6 +941,15 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
             else SAPC(64, _Float16);
         }
 #undef SAPC
+    } else if (two64) {
+        const int anti = c->t_antiperiodic ? 1 : 0;
+#define SAPC64(VB)                                                                                             \
+    sapc64_kernel<VB><<<grid, 2 * VB, 2 * ldsc, c->stream>>>(g, (const double2 *)c->U64, (const double2 *)c->A64, b, z, \
+                                                             col, mr, sre, sim, anti)
+        if (g.Vb == 256) SAPC64(256);
+        else if (g.Vb == 128) SAPC64(128);
+        else SAPC64(64);
+#undef SAPC64
     } else if (prec == MGDD_F64) {
         sap_colour_kernel<double><<<grid, g.Vb, lds, c->stream>>>(g, (const double2 *)c->U64, (const double2 *)c->A64,
                                                                   (const double2 *)b, (double2 *)z, col, mr, sre, sim);
@@ -921,12 +967,12 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
                                                                  (const float2 *)b, (float2 *)z, col, mr, (float)sre,
                                                                  (float)sim);
     }
-    // per site of the colour: links (two rows each on the two-lanes kernel,
-    // which rebuilds the third) and clover term once per launch; z in, b in
-    // and z out per field (the halo comes from cache). FP16: FP32 links.
-    const double lc = prec == MGDD_F64 ? 1152.0 : lanes == 2 ? 480.0 : 576.0, sp = 3.0 * 12 * csize(prec);
+    // per site of the colour: links (two rows each where the third is
+    // rebuilt) and clover term once per launch; z in, b in and z out per
+    // field (the halo comes from cache). FP16: FP32 links.
+    const double lc = prec == MGDD_F64 ? (two64 ? 960.0 : 1152.0) : lanes == 2 ? 480.0 : 576.0, sp = 3.0 * 12 * csize(prec);
     kt_end(c, slot, KF_SAP, prec, (double)nblocks * g.Vb * nrhs, (double)nblocks * g.Vb * (lc + sp * nrhs));
-    return hip_check(c, hipGetLastError(), "sap kernel");
+    return rc ? rc : hip_check(c, hipGetLastError(), "sap kernel");
 }
 
 int launch_sap(Ctx *c, int prec, int nrhs, int nsweeps, int mr, double sre, double sim, const void *b, void *z) {

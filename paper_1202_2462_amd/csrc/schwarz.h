@@ -22,4 +22,10 @@ size_t schwarz_work_bytes(const Ctx *c, int prec, int nrhs, const SchwarzOpts &o
 int launch_schwarz(Ctx *c, int prec, int nrhs, const SchwarzOpts &o, double sre, double sim, const void *b, void *z,
                    void *work);
 
+// One FP32 or half-storage colour step with MR(mr) block solves, one lane per
+// site, for special unitary links (sap_site.hip); LDS bytes of a workgroup for
+// blocks of Vb sites.
+size_t sap_site_lds(int Vb);
+int launch_sap_site(Ctx *c, int prec, int nrhs, int col, int mr, double sre, double sim, const void *b, void *z);
+
 }  // namespace mgdd
