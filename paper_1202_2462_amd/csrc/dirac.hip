@@ -116,6 +116,162 @@ __global__ __launch_bounds__(TPB) void dirac_widen_kernel(Geom g, const double2 
     store_spinor<double, true>(o, d, res);
 }
 
+// ---- several right-hand sides, blocks of TPB sites: R of them per thread
+
+// raw components of a field stored as S
+template <typename S> struct RawView {
+    rsrc_t r;
+    unsigned cs;
+    __device__ RawView(const C<S> *base, size_t V) : r(make_rsrc(base, 12 * V * sizeof(C<S>))) {
+        cs = (unsigned)(V * sizeof(C<S>));
+    }
+    __device__ C<S> ld(int comp, int site) const {
+        const unsigned vo = (unsigned)site * (unsigned)sizeof(C<S>), so = comp * cs;
+        if constexpr (sizeof(S) == 2) return __builtin_bit_cast(C<S>, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+        else return BIO<S>::ld(r, vo, so);
+    }
+};
+
+// a where b is +0, b where a is
+__device__ inline half_cx either(half_cx a, half_cx b) {
+    return __builtin_bit_cast(half_cx, __builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b));
+}
+__device__ inline float2 either(float2 a, float2 b) {
+    const uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    return __builtin_bit_cast(float2, make_uint2(x.x | y.x, x.y | y.y));
+}
+__device__ inline double2 either(double2 a, double2 b) {
+    const uint4 x = __builtin_bit_cast(uint4, a), y = __builtin_bit_cast(uint4, b);
+    return __builtin_bit_cast(double2, make_uint4(x.x | y.x, x.y | y.y, x.z | y.z, x.w | y.w));
+}
+
+constexpr int OUT = TPB, RS = TPB + 2;   // the zero slot; LDS sites of a component
+
+template <typename T, typename S, bool RECON, int R> struct BlockHops {
+    LinkViews<T> U;
+    const C<S> *in, *sp;
+    size_t V;
+    int d, ln[8], nd[8], nb[8];
+    T sf, sb;
+    C<T> acc[R][12], u[9], gu[9];
+    C<S> gm[12];
+    __device__ BlockHops(const C<T> *Up, size_t v) : U(Up, v), V(v) {}
+
+    // neighbour M's spinor of right-hand side q when it is outside the block
+    // (0 otherwise: an offset past the field)
+    template <int M> __device__ void load_spinor(int q) {
+        const RawView<S> f(in + (size_t)q * 12 * V, V);
+#pragma unroll
+        for (int k = 0; k < 12; k++) gm[k] = f.ld(k, nd[M]);
+    }
+    template <int M> __device__ void load_link() {
+#pragma unroll
+        for (int k = 0; k < (RECON ? 6 : 9); k++) gu[k] = U.template get<M / 2>().ld(k, M & 1 ? nb[M] : d);
+    }
+    // hop M of every right-hand side; the reads of the next one's operands from
+    // memory run under its arithmetic (the branch, always taken, keeps the
+    // scheduler from holding more than one step's operands)
+    template <int M> __device__ void step() {
+#pragma unroll
+        for (int q = 0; q < R; q++)
+            if (opaque_zero() == 0) {
+                if (q == 0) {
+#pragma unroll
+                    for (int k = 0; k < (RECON ? 6 : 9); k++) u[k] = gu[k];
+                }
+                C<T> psi[12];
+#pragma unroll
+                for (int k = 0; k < 12; k++) psi[k] = widen_to(either(sp[(12 * q + k) * RS + ln[M]], gm[k]), T());
+                __builtin_amdgcn_sched_barrier(0);
+                if (q + 1 < R) {
+                    load_spinor<M>(q + 1);
+                } else if (M < 7) {
+                    load_link<(M + 1) & 7>();
+                    load_spinor<(M + 1) & 7>(0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (q == 0 && RECON) su3_row2<T>(u, M == 6 ? sf : M == 7 ? sb : (T)1);
+                hop<T, M / 2, !(M & 1)>(acc[q], u, psi);
+            }
+    }
+};
+
+// The apply for nrhs > 1: a link and the clover term are read, and the link's
+// third row rebuilt, once for R right-hand sides; the workgroup's spinors are in
+// LDS as they are stored (S), a neighbour outside the block is the zero slot
+// there and comes from memory, one step ahead. Every right-hand side goes
+// through the operations of dirac_kernel in the same order, so that it gets
+// the same bits from both. Bound: what misses L2. The workgroups in flight
+// hold as much in LDS as the 4 MB of L2, so that most of a block's halo comes
+// from beyond it (24^3 x 48, FP32, 12 right-hand sides: 4.0 GB read of the
+// 1.1 GB that are there once). Before (R = 1) and after, 24^3 x 48: FP32 12
+// right-hand sides 1135 -> 862 us, half storage 861 -> 588, FP64 4 621 -> 520.
+// Not faster: the groups of one range of sites one after the other instead of
+// together, links or clover term with the non-temporal policy (2 - 10 % slower).
+template <typename T, typename S, typename O, bool RECON, int R, int WAVES>
+__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(WAVES))) void dirac_block_kernel(
+    Geom g, const C<T> *__restrict__ Up, const C<T> *__restrict__ Ap, const C<S> *__restrict__ in, C<O> *__restrict__ out,
+    int nrhs, int ngr, int nwg, int antiperiodic) {
+    __shared__ C<S> sp[R * 12 * RS];
+    const int w = xcd_block(nwg);
+    const int gr = w % ngr, r0 = min(gr * R, nrhs - R), first = gr * R - r0;   // the last group overlaps the one before
+    const int d = site_in_lex_block_order(g, (w / ngr) * TPB + threadIdx.x), l = d & (TPB - 1);
+    const size_t V = g.V;
+    BlockHops<T, S, RECON, R> H(Up, V);
+    H.in = in + (size_t)r0 * 12 * V;
+    H.sp = sp;
+    H.d = d;
+    site_neighbours(g, d, H.nb);
+#pragma unroll
+    for (int m = 0; m < 8; m++) {
+        const bool inside = (H.nb[m] ^ d) < TPB;
+        H.ln[m] = inside ? H.nb[m] & (TPB - 1) : OUT;
+        H.nd[m] = inside ? 12 * g.V : H.nb[m];
+    }
+    H.sf = H.sb = 1;
+    if (RECON) time_link_signs<T>(g, d, antiperiodic, H.sf, H.sb);
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+        const RawView<S> f(H.in + (size_t)q * 12 * V, V);
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            sp[(12 * q + k) * RS + l] = f.ld(k, d);
+            H.acc[q][k] = mk<T>(0, 0);
+        }
+    }
+    if (l < 12 * R) sp[l * RS + OUT] = mk<S>(0, 0);
+    H.template load_link<0>();
+    H.template load_spinor<0>(0);
+    __syncthreads();
+    H.template step<0>();
+    H.template step<1>();
+    H.template step<2>();
+    H.template step<3>();
+    H.template step<4>();
+    H.template step<5>();
+    H.template step<6>();
+    H.template step<7>();
+    const CloverViews<T> A(Ap, V);
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        C<T> p[18];
+#pragma unroll
+        for (int k = 0; k < 18; k++) p[k] = (h ? A.a1 : A.a0).ld(k, d);
+#pragma unroll
+        for (int q = 0; q < R; q++)
+            if (q >= first) {
+                C<T> psi[6], res[6];
+#pragma unroll
+                for (int k = 0; k < 6; k++) psi[k] = widen_to(sp[(12 * q + 6 * h + k) * RS + l], T());
+                herm6_mv<T>(p, psi, res);
+                const typename SpinorView<T, O>::type o(out + (size_t)(r0 + q) * 12 * V, V, 12);
+#pragma unroll
+                for (int k = 0; k < 6; k++)
+                    o.template st<true>(6 * h + k, d, csub(res[k], cscale(H.acc[q][6 * h + k], (T)0.5)));
+            }
+    }
+}
+
 }  // namespace
 
 // algorithmic bytes of one apply per site: links (two rows of each when they
@@ -136,6 +292,30 @@ static int dirac_staged(Ctx *c) {
     return c->dirac_stage >= 0 && c->g.Vb == TPB ? 1 : 0;
 }
 
+// Right-hand sides per thread, 1: dirac_kernel / dirac_widen_kernel. FP32
+// arithmetic: the count of 2 and 3 that takes less (24^3 x 48, 2: 71 us, 3: 66
+// us each, the last group's repeated ones included; against 93). FP64: 2 (130
+// against 155 us each), the one repeated of an odd count costing more than
+// that up to 5 of them (3: 490 against 484 us). With fewer than 192 workgroups
+// the chip is better filled by one each (8^4, FP32, 12 right-hand sides, 64
+// workgroups: 18 against 11 us; 8^2 x 16^2, 6: 128 18.6, 192 14.3 against 18.4).
+static int rhs_per_thread(const Ctx *c, bool f64, int nrhs) {
+    const int two = (nrhs + 1) / 2, three = (nrhs + 2) / 3, nblk = c->g.V / TPB;
+    if (nrhs < 2 || (f64 && nrhs % 2 && nrhs < 7)) return 1;
+    if (!f64 && 66 * 3 * three <= 71 * 2 * two && nblk * three >= 192) return 3;
+    return nblk * two >= 192 ? 2 : 1;
+}
+
+template <typename T, typename S, typename O, int R, int WAVES>
+static void launch_block(Ctx *c, const void *U, const void *A, const void *in, void *out, int nrhs) {
+    const int ngr = (nrhs + R - 1) / R, nwg = c->g.V / TPB * ngr, anti = c->t_antiperiodic ? 1 : 0;
+#define BLOCK(RECON)                                                                                            \
+    dirac_block_kernel<T, S, O, RECON, R, WAVES><<<nwg, TPB, 0, c->stream>>>(                                   \
+        c->g, (const C<T> *)U, (const C<T> *)A, (const C<S> *)in, (C<O> *)out, nrhs, ngr, nwg, anti)
+    if (c->links_su3) BLOCK(true); else BLOCK(false);
+#undef BLOCK
+}
+
 int launch_dirac_widen(Ctx *c, int nrhs, const void *in32, void *out64, int in_prec) {
     int nwg = ((c->g.V + TPB - 1) / TPB) * nrhs;
     const int anti = c->t_antiperiodic ? 1 : 0;
@@ -143,6 +323,10 @@ int launch_dirac_widen(Ctx *c, int nrhs, const void *in32, void *out64, int in_p
     if (st < 0) return MGDD_ESHAPE;
     const bool stage = st == 1;
     const int slot = kt_begin(c);
+    if (stage && rhs_per_thread(c, true, nrhs) == 2) {   // 16^3 x 32, 4 right-hand sides: 102 -> 78 us
+        if (in_prec == MGDD_F16) launch_block<double, _Float16, double, 2, 1>(c, c->U64, c->A64, in32, out64, nrhs);
+        else launch_block<double, float, double, 2, 1>(c, c->U64, c->A64, in32, out64, nrhs);
+    } else {
 #define WIDEN(R, G, S)                                                                                                \
     dirac_widen_kernel<R, G, S><<<nwg, TPB, 0, c->stream>>>(c->g, (const double2 *)c->U64, (const double2 *)c->A64,  \
                                                             (const C<S> *)in32, (double2 *)out64, nrhs, nwg, anti)
@@ -155,6 +339,7 @@ int launch_dirac_widen(Ctx *c, int nrhs, const void *in32, void *out64, int in_p
         }                                                                                                             \
     } while (0)
     if (in_prec == MGDD_F16) WIDEN_S(_Float16); else WIDEN_S(float);
+    }
 #undef WIDEN_S
 #undef WIDEN
     kt_end(c, slot, KF_DIRAC, MGDD_F64, (double)c->g.V * nrhs,
@@ -181,7 +366,14 @@ int launch_dirac(Ctx *c, int prec, int nrhs, const void *in, void *out) {
             if (stage) DIRAC(T, T, false, true); else DIRAC(T, T, false, false);                                      \
         }                                                                                                             \
     } while (0)
-    if (prec == MGDD_F64) {
+    const int per = stage ? rhs_per_thread(c, prec == MGDD_F64, nrhs) : 1;
+    if (per > 1) {
+        if (prec == MGDD_F64) launch_block<double, double, double, 2, 1>(c, c->U64, c->A64, in, out, nrhs);
+        else if (prec == MGDD_F32 && per == 2) launch_block<float, float, float, 2, 3>(c, c->U32, c->A32, in, out, nrhs);
+        else if (prec == MGDD_F32) launch_block<float, float, float, 3, 2>(c, c->U32, c->A32, in, out, nrhs);
+        else if (per == 2) launch_block<float, _Float16, _Float16, 2, 3>(c, c->U32, c->A32, in, out, nrhs);
+        else launch_block<float, _Float16, _Float16, 3, 2>(c, c->U32, c->A32, in, out, nrhs);
+    } else if (prec == MGDD_F64) {
         DIRAC_STAGED(double);
     } else if (prec == MGDD_F32) {
         DIRAC_STAGED(float);

@@ -309,6 +309,7 @@ __device__ inline void hop_sum(const LinkViews<T> &U, const FV &f, int d, const 
 __device__ inline float2 widen_to(float2 v, float) { return v; }
 __device__ inline double2 widen_to(double2 v, double) { return v; }
 __device__ inline double2 widen_to(float2 v, double) { return make_double2((double)v.x, (double)v.y); }
+__device__ inline float2 widen_to(half_cx v, float) { return make_float2((float)v.x, (float)v.y); }
 __device__ inline double2 widen_to(half_cx v, double) { return make_double2((double)v.x, (double)v.y); }
 
 template <typename T, typename S, int MU, bool FWD, bool RECON, int NT>
