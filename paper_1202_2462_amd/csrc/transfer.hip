@@ -100,10 +100,17 @@ __global__ __launch_bounds__(TPB) void build_P_kernel(int V, int Va, int N, cons
 // LDS slots); within the panel a column's norm and its products with the
 // later ones are. Each column still has the earlier ones taken off one after
 // the other, so this is modified Gram-Schmidt in column order.
+// The test vectors are read from tv and copied to kept (unless null), and P is
+// written in every precision while its column is in registers.
 // Bound: the reads of the earlier columns (from the Infinity Cache: 256
-// workgroups' columns do not fit L2) and the latency of the sums. 24^3 x 48
-// lattice, 3x4x4x4 aggregates, N = 21: 4.3 ms; one column at a time read
-// every earlier column N times over (60 GB) and took 10.8 ms.
+// workgroups' columns do not fit L2), the streams of tv and P, and the latency
+// of the sums. An aggregate's sites cover lines of the field only in part, so
+// neighbouring aggregates run on one XCD at the same time, where its L2 puts the
+// lines together (24^3 x 48 lattice, 3x4x4x4 aggregates, N = 21: 5.5 ms against
+// 8.9 in the order of the launch; with the non-temporal policy, which gives the
+// lines up before they are whole, 7.9 in that order). Separate copies and
+// conversions took 3.3 ms more than the 4.3 ms without them; one column at a
+// time, which reads every earlier column N times over, 10.8 ms.
 constexpr int PANEL = 4;
 
 // v[i] <- the sum of v[i] over the workgroup, i < 8
@@ -120,32 +127,41 @@ __device__ inline void block_sum8(double *v, double *red) {
 }
 
 __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(2))) void build_P_panel_kernel(
-    int V, int Va, int N, const int *__restrict__ agg_sites, double2 *__restrict__ P, int *__restrict__ flag) {
+    int V, int Va, int N, const int *__restrict__ agg_sites, const double2 *tv, double2 *kept, double2 *P,
+    float2 *__restrict__ P32, half_cx *__restrict__ P16, int *__restrict__ flag) {
     __shared__ double red[2][8 * (TPB / 64)];
-    const int a = blockIdx.x, chi = blockIdx.y;
+    const int wg = xcd_block(gridDim.x), Vc = gridDim.x >> 1, chi = wg >= Vc, a = wg - chi * Vc;
     const bool active = (int)threadIdx.x < Va;
     const int d = active ? agg_sites[(size_t)a * Va + threadIdx.x] : 0;
     const size_t fs = (size_t)12 * V;  // field stride
-    double2 *Pd = P + (size_t)6 * chi * V + d;
+    const size_t o = (size_t)6 * chi * V + d;
     int slot = 0;
-    auto load = [&](int k, double2 *v) {
+    auto load = [&](const double2 *F, int k, double2 *v) {
 #pragma unroll
-        for (int c = 0; c < 6; c++) v[c] = active && k < N ? Pd[(size_t)k * fs + (size_t)c * V] : make_double2(0, 0);
+        for (int c = 0; c < 6; c++) v[c] = active && k < N ? F[o + (size_t)k * fs + (size_t)c * V] : make_double2(0, 0);
     };
     for (int k0 = 0; k0 < N; k0 += PANEL) {
         double2 w[PANEL][6], q[6], qn[6];
         double n0[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < PANEL; i++) {
-            load(k0 + i, w[i]);
+            load(tv, k0 + i, w[i]);
 #pragma unroll
             for (int c = 0; c < 6; c++) n0[i] += w[i][c].x * w[i][c].x + w[i][c].y * w[i][c].y;
         }
-        if (k0) load(0, q);
+        if (kept && active) {
+#pragma unroll
+            for (int i = 0; i < PANEL; i++)
+                if (k0 + i < N) {
+#pragma unroll
+                    for (int c = 0; c < 6; c++) kept[o + (size_t)(k0 + i) * fs + (size_t)c * V] = w[i][c];
+                }
+        }
+        if (k0) load(P, 0, q);
         block_sum8(n0, red[slot]);
         slot ^= 1;
         for (int j = 0; j < k0; j++) {
-            load(j + 1 < k0 ? j + 1 : j, qn);   // while column j is used
+            load(P, j + 1 < k0 ? j + 1 : j, qn);   // while column j is used
             double r[2 * PANEL];
 #pragma unroll
             for (int i = 0; i < PANEL; i++) {
@@ -196,7 +212,16 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(2))) void b
                     cfma(w[m][c], make_double2(-r[2 * m] * inv, -r[2 * m + 1] * inv), w[i][c]);
             if (active) {
 #pragma unroll
-                for (int c = 0; c < 6; c++) Pd[(size_t)(k0 + i) * fs + (size_t)c * V] = w[i][c];
+                for (int c = 0; c < 6; c++) {
+                    const size_t e = o + (size_t)(k0 + i) * fs + (size_t)c * V;
+                    const float2 f = make_float2((float)w[i][c].x, (float)w[i][c].y);
+                    half_cx h;
+                    h.x = (_Float16)w[i][c].x;
+                    h.y = (_Float16)w[i][c].y;
+                    P[e] = w[i][c];
+                    P32[e] = f;
+                    P16[e] = h;
+                }
             }
         }
     }
@@ -574,21 +599,42 @@ int transfer_setup(Ctx *c, const int *agg, int N) {
     return MGDD_OK;
 }
 
+// device memory, aligned for 16-byte loads
+static bool kernel_readable(const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && !((uintptr_t)p & 15);
+}
+
 int launch_build_P(Ctx *c, const void *tv64) {
     Level1 &L1 = c->c;
     const Geom &g = c->g;
-    size_t fsz = (size_t)L1.N * 12 * g.V;
-    int rc = hip_check(c, hipMemcpyAsync(L1.P64, tv64, fsz * 16, hipMemcpyDeviceToDevice, c->stream), "copy");
-    if (!rc && tv64 != L1.tv64)
-        rc = hip_check(c, hipMemcpyAsync(L1.tv64, tv64, fsz * 16, hipMemcpyDeviceToDevice, c->stream), "copy");
-    if (rc) return rc;
+    const size_t fsz = (size_t)L1.N * 12 * g.V;
+    const bool panel = L1.Va <= TPB, keep = tv64 != L1.tv64;
+    // the panel kernel reads the caller's vectors itself, keeps the copy of
+    // them and writes every form of P (24^3 x 48, N = 21: 5.5 ms; with two
+    // copies before and two conversions after it 7.6 ms); a copy also takes
+    // memory that a kernel's 16-byte loads may not
+    const bool direct = panel && (!keep || kernel_readable(tv64));
+    int rc = MGDD_OK;
+    if (!direct) {
+        rc = hip_check(c, hipMemcpyAsync(L1.P64, tv64, fsz * 16, hipMemcpyDeviceToDevice, c->stream), "copy");
+        if (!rc && keep)
+            rc = hip_check(c, hipMemcpyAsync(L1.tv64, tv64, fsz * 16, hipMemcpyDeviceToDevice, c->stream), "copy");
+        if (rc) return rc;
+    }
     int *flag = (int *)ensure_scratch(c, sizeof(int));
     if (!flag) return MGDD_ENOMEM;
     rc = hip_check(c, hipMemsetAsync(flag, 0, sizeof(int), c->stream), "memset");
     if (rc) return rc;
-    if (L1.Va <= TPB)
-        build_P_panel_kernel<<<dim3(L1.Vc, 2), (unsigned)((L1.Va + 63) / 64 * 64), 0, c->stream>>>(
-            g.V, L1.Va, L1.N, L1.agg_sites, (double2 *)L1.P64, flag);
+    if (panel)
+        build_P_panel_kernel<<<2 * L1.Vc, (unsigned)((L1.Va + 63) / 64 * 64), 0, c->stream>>>(
+            g.V, L1.Va, L1.N, L1.agg_sites, (const double2 *)(direct ? tv64 : L1.P64),
+            direct && keep ? (double2 *)L1.tv64 : nullptr,
+            (double2 *)L1.P64, (float2 *)L1.P32, (half_cx *)L1.P16, flag);
     else
         build_P_kernel<<<dim3(L1.Vc, 2), TPB, 0, c->stream>>>(g.V, L1.Va, L1.N, L1.agg_sites, (double2 *)L1.P64, flag);
     rc = hip_check(c, hipGetLastError(), "build_P kernel");
@@ -598,8 +644,10 @@ int launch_build_P(Ctx *c, const void *tv64) {
     if (!rc) rc = hip_check(c, hipStreamSynchronize(c->stream), "sync");
     if (rc) return rc;
     if (hflag) return fail(c, MGDD_ERANK, "test vectors are rank deficient on some aggregate");
-    rc = launch_convert(c, MGDD_F64, MGDD_F32, fsz, L1.P64, L1.P32);
-    if (!rc) rc = launch_convert(c, MGDD_F64, MGDD_F16, fsz, L1.P64, L1.P16);
+    if (!panel) {
+        rc = launch_convert(c, MGDD_F64, MGDD_F32, fsz, L1.P64, L1.P32);
+        if (!rc) rc = launch_convert(c, MGDD_F64, MGDD_F16, fsz, L1.P64, L1.P16);
+    }
     return rc;
 }
 

@@ -48,3 +48,28 @@ def test_rank_deficiency_within_and_across_panels(copy):
         lat.build_P(agg, lat.pack(tv, F64))
     assert e.value.code == ERANK
     lat.close()
+
+
+@pytest.mark.parametrize("agg", [(3, 4, 4, 4), (12, 4, 4, 8)])
+def test_test_vectors_off_the_16_byte_grid(agg):
+    """Vectors that kernels cannot read in 16-byte loads give the same P in every
+    precision and the same kept copy, also in aggregates past a workgroup."""
+    import torch
+    from paper_1202_2462_amd.mgdd import F16, F32, F64
+    dims, N = (12, 4, 4, 8), 6
+    lat = lattice(problem(dims, seed=21, m0=0.1), (2, 4, 4, 4))
+    tv = lat.pack(latgen.gaussian_fields(dims, N, 25), F64)
+    shifted = torch.empty(tv.numel() + 1, dtype=tv.dtype, device=tv.device)[1:].view(tv.shape)
+    shifted.copy_(tv)
+    assert shifted.data_ptr() % 16 == 8
+    c = latgen.gaussian_fields((12 // agg[0], 4 // agg[1], 4 // agg[2], 8 // agg[3]), 1, 26)   # (1, Vc, 4, 3): N = 6
+    dev = torch.tensor(np.stack([c.real, c.imag], -1).reshape(1, -1, 2, N, 2), device="cuda")
+    seen = []
+    for vectors in (tv, shifted):
+        lat.build_P(agg, vectors)
+        say("kept copy and P", agg)
+        assert bool((lat.test_vectors() == tv).all())
+        seen.append([lat.prolong(dev.to(torch.float64 if p == F64 else torch.float32), lat.field(p, 1)) for p in (F64, F32, F16)])
+    for x, y in zip(*seen):
+        assert bool((x == y).all())
+    lat.close()
