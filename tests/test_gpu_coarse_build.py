@@ -1,7 +1,7 @@
 """GPU parity of the coarse operator's build at the edges of its tiles: vector
 counts around 16 and 32 (row tiles), aggregates whose site or face count is
 not a multiple of 4, with extents of 1, larger than 256 sites and as large as
-the lattice."""
+the lattice, on both sides of the 64 sites from which another kernel is used."""
 import numpy as np
 import pytest
 
@@ -20,6 +20,12 @@ pytestmark = pytest.mark.gpu
     ((4, 4, 4, 4), (4, 4, 4, 4), (1, 1, 1, 1), 1),
     ((8, 8, 4, 8), (4, 4, 4, 4), (4, 8, 4, 4), 21),
     ((8, 4, 4, 4), (4, 4, 4, 4), (8, 4, 4, 4), 9),
+    ((12, 12, 4, 4), (2, 2, 4, 4), (3, 3, 4, 2), 25),
+    ((20, 4, 4, 4), (2, 4, 4, 4), (5, 4, 4, 1), 8),
+    ((8, 4, 4, 4), (4, 4, 4, 4), (4, 4, 4, 1), 32),
+    ((8, 4, 4, 4), (4, 4, 4, 4), (4, 4, 2, 2), 1),
+    ((12, 12, 4, 4), (2, 2, 4, 4), (6, 3, 2, 4), 24),
+    ((12, 4, 4, 4), (2, 4, 4, 4), (3, 4, 4, 1), 20),
 ])
 def test_coarse_operator_tile_edges(dims, block, agg, N):
     from paper_1202_2462_amd.mgdd import F32, F64
