@@ -74,19 +74,36 @@ __global__ __launch_bounds__(TPB) void multidot_kernel(size_t n, PL xs, int nvec
     }
 }
 
-// out[q] = sum_k part[q * nwg + k] (q = i * nseg + s): one 64-lane wave per q,
-// lane l adding the partials k = l, l + 64, ... in order, then a butterfly.
-__global__ __launch_bounds__(64) void finish_kernel(int nwg, const double2 *__restrict__ part, double2 *__restrict__ out) {
-    const int i = blockIdx.x, lane = threadIdx.x;
+// out[q] = sum_k part[q * nwg + k] (q = i * nseg + s): one workgroup per q,
+// thread l adding the partials k = l, l + FTPB, ... in order, then a butterfly
+// in each wave and the waves in order. Bound: latency, so eight partials are
+// loaded at a time (from clamped places): 8192 of them 4.5 us, with one wave
+// and one load at a time 16 us.
+constexpr int FTPB = 256;
+__global__ __launch_bounds__(FTPB) void finish_kernel(int nwg, const double2 *__restrict__ part, double2 *__restrict__ out) {
+    __shared__ double red[FTPB / 64][2];
+    const double2 *p = part + (size_t)blockIdx.x * nwg;
     double a = 0, b = 0;
-    for (int k = lane; k < nwg; k += 64) {
-        double2 v = part[(size_t)i * nwg + k];
-        a += v.x;
-        b += v.y;
+    for (int k = threadIdx.x; k < nwg; k += 8 * FTPB) {
+        double2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = p[min(k + u * FTPB, nwg - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const bool in = k + u * FTPB < nwg;
+            a += in ? v[u].x : 0.0;
+            b += in ? v[u].y : 0.0;
+        }
     }
     a = wave_sum(a);
     b = wave_sum(b);
-    if (lane == 0) out[i] = make_double2(a, b);
+    const int wv = threadIdx.x >> 6;
+    if (!(threadIdx.x & 63)) { red[wv][0] = a; red[wv][1] = b; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < FTPB / 64; w++) { a += red[w][0]; b += red[w][1]; }
+        out[blockIdx.x] = make_double2(a, b);
+    }
 }
 
 // y = beta y + alpha sum_i coef[i] x_i
@@ -624,7 +641,7 @@ int blas_multidot(Ctx *c, int px, int pw, size_t n, const void *const *xs, int n
         else MD(double, float);
 #undef MD
 #undef MD1
-        finish_kernel<<<nv * nseg, 64, 0, c->stream>>>(nwg, part, out + (size_t)i0 * nseg);
+        finish_kernel<<<nv * nseg, FTPB, 0, c->stream>>>(nwg, part, out + (size_t)i0 * nseg);
         int rc = hip_check(c, hipGetLastError(), "multidot");
         if (rc) return rc;
     }
@@ -688,7 +705,7 @@ int blas_update_dot(Ctx *c, int p, size_t n, const void *const *xs, int nvec, co
 #undef UD
 #undef UD1
     const int nout = mode == 1 ? 1 : nvec;
-    finish_kernel<<<nout * nseg, 64, 0, c->stream>>>(nwg, part, out);
+    finish_kernel<<<nout * nseg, FTPB, 0, c->stream>>>(nwg, part, out);
     return hip_check(c, hipGetLastError(), "update_dot");
 }
 
@@ -723,8 +740,8 @@ int blas_dots2(Ctx *c, size_t n, const void *const *xs, int nvec, const void *w,
 #define D2(NGT, GT)     dots2_kernel<NGT, GT><<<grid, TPB, 0, c->stream>>>(n, pl, nv, (const double2 *)w, (const double2 *)v, part)
         if (nv <= 4) D2(4, 1); else if (nv <= 8) D2(8, 1); else if (nv <= 16) D2(8, 2); else D2(8, 4);
 #undef D2
-        finish_kernel<<<nv * nseg, 64, 0, c->stream>>>(nwg, part, out_w + (size_t)i0 * nseg);
-        finish_kernel<<<nv * nseg, 64, 0, c->stream>>>(nwg, part + (size_t)nv * nseg * nwg, out_v + (size_t)i0 * nseg);
+        finish_kernel<<<nv * nseg, FTPB, 0, c->stream>>>(nwg, part, out_w + (size_t)i0 * nseg);
+        finish_kernel<<<nv * nseg, FTPB, 0, c->stream>>>(nwg, part + (size_t)nv * nseg * nwg, out_v + (size_t)i0 * nseg);
         int rc = hip_check(c, hipGetLastError(), "dots2");
         if (rc) return rc;
     }
@@ -746,7 +763,7 @@ int blas_dcgs_update(Ctx *c, size_t n, const void *const *xs, int nvec, const do
 #define DU(NGT, GT)                                                                                                      dcgs_update_kernel<NGT, GT><<<grid, TPB, 0, c->stream>>>(n, pl, nv, i0, nvec, coef, last, (double2 *)v,                                                                      (double2 *)w, part)
         if (nv <= 4) DU(4, 1); else if (nv <= 8) DU(8, 1); else if (nv <= 16) DU(8, 2); else DU(8, 4);
 #undef DU
-        if (last) finish_kernel<<<nseg, 64, 0, c->stream>>>(nwg, part, nrm);
+        if (last) finish_kernel<<<nseg, FTPB, 0, c->stream>>>(nwg, part, nrm);
         int rc = hip_check(c, hipGetLastError(), "dcgs_update");
         if (rc) return rc;
         i0 += nv;
