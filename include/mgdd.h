@@ -125,9 +125,10 @@ int mgdd_set_allocator(mgdd_ctx *ctx, mgdd_alloc_fn alloc, mgdd_free_fn free_fn,
  *     special unitary links) or 4 (four lanes per site, the whole links
  *     staged). Half-precision storage runs with 0 or 2 only; FP64 sweeps
  *     take no notice of it.
- *   dirac_stage: Wilson-clover apply with blocks of 256 sites: 0 automatic
- *     (the workgroup's block of spinors staged in LDS), 1 staged, -1 not
- *     staged (every neighbour read from memory).
+ *   dirac_stage: Wilson-clover apply: 0 automatic (four lanes per site up to
+ *     16384 sites of all right-hand sides; else, with blocks of 256 sites,
+ *     the workgroup's block of spinors staged in LDS), 1 staged, -1 not
+ *     staged (every neighbour read from memory). The same bits from all.
  * A variant the context cannot run fails at launch with MGDD_ESHAPE.
  * Errors: MGDD_EINVAL (values outside these sets). */
 typedef struct {

@@ -2,6 +2,7 @@
 // site-major loads of the 8 neighbour spinors and links, spin projection to
 // half spinors before the SU(3) products.
 #include "dirac.h"
+#include "lanes.h"
 #include "stencil.h"
 
 namespace mgdd {
@@ -272,6 +273,149 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
     }
 }
 
+// ---- few sites: four lanes per site, one per direction
+
+// h = (1 -+ gamma_mu) psi, upper half, and d, the 12 components that a hop with w
+// = U h (or U^H h) adds to the sum: the two halves of hop() in stencil.h
+template <typename T, int MU, bool FWD> __device__ inline void quad_project(const C<T> *psi, C<T> *h) {
+    const C<T> *u0 = psi, *u1 = psi + 3, *l0 = psi + 6, *l1 = psi + 9;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const C<T> f0 = MU == 0 ? ci(l1[a]) : MU == 1 ? l1[a] : MU == 2 ? ci(l0[a]) : l0[a];
+        const C<T> f1 = MU == 0 ? ci(l0[a]) : MU == 1 ? cneg(l0[a]) : MU == 2 ? cneg(ci(l1[a])) : l1[a];
+        h[a] = FWD ? cadd(u0[a], f0) : csub(u0[a], f0);
+        h[3 + a] = FWD ? cadd(u1[a], f1) : csub(u1[a], f1);
+    }
+}
+template <typename T, int MU, bool FWD> __device__ inline void quad_lower(const C<T> *w, C<T> *d) {
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        // B^H w: (i w1, i w0), (w1, -w0), (i w0, -i w1), (-w0, -w1)
+        const C<T> b0 = MU == 0 ? ci(w[3 + a]) : MU == 1 ? w[3 + a] : MU == 2 ? ci(w[a]) : cneg(w[a]);
+        const C<T> b1 = MU == 0 ? ci(w[a]) : MU == 1 ? cneg(w[a]) : MU == 2 ? cneg(ci(w[3 + a])) : cneg(w[3 + a]);
+        d[a] = FWD ? cneg(b0) : b0;
+        d[3 + a] = FWD ? cneg(b1) : b1;
+    }
+}
+
+// Lane mu of a site forms its forward and its backward hop, all its operands
+// in flight at once; the sum then goes from lane to lane in the order of
+// dirac_kernel's, so that both give the same bits. A lane finishes three
+// components of the result. Bound: the latency of one chain of loads, where
+// dirac_kernel has eight (and 16 of 256 CUs at work on 8^4 sites): 8^4, FP64, 6.0 us
+// against 10.3.
+constexpr int QSITES = 16;   // sites of a workgroup, one wave
+template <typename T, typename S, typename O, bool RECON>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) void dirac_quad_kernel(
+    Geom g, const C<T> *__restrict__ Up, const C<T> *__restrict__ Ap, const C<S> *__restrict__ in, C<O> *__restrict__ out,
+    int antiperiodic) {
+    __shared__ C<T> sum[12][QSITES];
+    const int lane = threadIdx.x, m = lane & 3, ls = lane >> 2, h = m >> 1;
+    const int i = blockIdx.x * QSITES + ls, d = i < g.V ? i : g.V - 1;
+    const size_t V = g.V;
+    in += (size_t)blockIdx.y * 12 * V;
+    const int pos = d >> g.lgVb;
+    int x[4], nf, nb, t;
+    local_coords(g, d & (g.Vb - 1), x);
+    t = (int)((g.blk_coord[pos] >> 24) << g.lb[3]) + x[3];
+    {
+        int xf[4], xb[4];
+        bool fin = false, bin = false;
+#pragma unroll
+        for (int mu = 0; mu < 4; mu++) {
+            const int bm = 1 << g.lb[mu];
+            xf[mu] = mu == m ? (x[mu] + 1) & (bm - 1) : x[mu];
+            xb[mu] = mu == m ? (x[mu] - 1) & (bm - 1) : x[mu];
+            if (mu == m) {
+                fin = x[mu] + 1 < bm || g.nb[mu] == 1;
+                bin = x[mu] > 0 || g.nb[mu] == 1;
+            }
+        }
+        const int pf = g.blk_nbr[pos * 8 + 2 * m], pb = g.blk_nbr[pos * 8 + 2 * m + 1];
+        nf = ((fin ? pos : pf) << g.lgVb) + local_index(g, xf);
+        nb = ((bin ? pos : pb) << g.lgVb) + local_index(g, xb);
+    }
+    const T sf = antiperiodic && m == 3 && t == g.L[3] - 1 ? (T)-1 : (T)1;
+    const T sb = antiperiodic && m == 3 && t == 0 ? (T)-1 : (T)1;
+    C<S> rf[12], rb[12], ro[6];
+    C<T> uf[9], ub[9], p[18];
+    const C<T> *Um = Up + (size_t)(9 * m) * V, *Ah = Ap + (size_t)(18 * h) * V;
+#pragma unroll
+    for (int k = 0; k < 12; k++) rf[k] = in[(size_t)k * V + nf];
+#pragma unroll
+    for (int k = 0; k < (RECON ? 6 : 9); k++) uf[k] = Um[(size_t)k * V + d];
+#pragma unroll
+    for (int k = 0; k < 12; k++) rb[k] = in[(size_t)k * V + nb];
+#pragma unroll
+    for (int k = 0; k < (RECON ? 6 : 9); k++) ub[k] = Um[(size_t)k * V + nb];
+#pragma unroll
+    for (int k = 0; k < 6; k++) ro[k] = in[(size_t)(6 * h + k) * V + d];
+#pragma unroll
+    for (int k = 0; k < 18; k++) p[k] = Ah[(size_t)k * V + d];
+    __builtin_amdgcn_sched_barrier(0);
+    C<T> hf[6], hb[6], wf[6], wb[6], df[6], db[6];
+    {
+        C<T> pf[12], pb[12];
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+            pf[k] = widen_to(rf[k], T());
+            pb[k] = widen_to(rb[k], T());
+        }
+#define PROJECT(MU)                          \
+    if (m == MU) {                           \
+        quad_project<T, MU, true>(pf, hf);   \
+        quad_project<T, MU, false>(pb, hb);  \
+    }
+        PROJECT(0)
+        PROJECT(1)
+        PROJECT(2)
+        PROJECT(3)
+#undef PROJECT
+    }
+    if (RECON) {
+        su3_row2<T>(uf, sf);
+        su3_row2<T>(ub, sb);
+    }
+    su3_mv<T, false>(uf, hf, wf);
+    su3_mv<T, false>(uf, hf + 3, wf + 3);
+    su3_mv<T, true>(ub, hb, wb);
+    su3_mv<T, true>(ub, hb + 3, wb + 3);
+#define LOWER(MU)                           \
+    if (m == MU) {                          \
+        quad_lower<T, MU, true>(wf, df);    \
+        quad_lower<T, MU, false>(wb, db);   \
+    }
+    LOWER(0)
+    LOWER(1)
+    LOWER(2)
+    LOWER(3)
+#undef LOWER
+    C<T> acc[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        const C<T> a = k < 6 ? wf[k] : df[k - 6], b = k < 6 ? wb[k] : db[k - 6];
+        acc[k] = cadd(cadd(mk<T>(0, 0), a), b);
+#pragma unroll
+        for (int step = 0; step < 3; step++)   // from the lane before: lane 3 has the sum at the end
+            acc[k] = cadd(cadd(mk<T>(dpp_mov<0x90>(acc[k].x), dpp_mov<0x90>(acc[k].y)), a), b);
+    }
+    if (m == 3)
+#pragma unroll
+        for (int k = 0; k < 12; k++) sum[k][ls] = acc[k];
+    __syncthreads();
+    C<T> own[6], res[6];
+#pragma unroll
+    for (int k = 0; k < 6; k++) own[k] = widen_to(ro[k], T());
+    herm6_mv<T>(p, own, res);
+    const typename SpinorView<T, O>::type o(out + (size_t)blockIdx.y * 12 * V, V, 12);
+    if (i < g.V)
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const C<T> r = m & 1 ? res[3 + k] : res[k];
+            o.st_lane(k, d, (unsigned)(3 * m) * o.cs, csub(r, cscale(sum[3 * m + k][ls], (T)0.5)));
+        }
+}
+
 }  // namespace
 
 // algorithmic bytes of one apply per site: links (two rows of each when they
@@ -316,6 +460,26 @@ static void launch_block(Ctx *c, const void *U, const void *A, const void *in, v
 #undef BLOCK
 }
 
+// Four lanes per site up to 16384 sites of all right-hand sides together, where
+// the other kernels leave most CUs idle and take the time of their chain of
+// loads (8^4, 1 right-hand side, FP64 6.0 against 10.3 us, FP32 5.4 against 9.0,
+// half storage 5.5 / 8.9; 4: 9.8 / 12.0, 7.9 / 9.0, 7.2 / 8.8; 8^2 x 16^2: 9.1 /
+// 12.9, 7.7 / 9.9, 7.0 / 9.2). Past that its four lanes per site, each with the
+// registers of a wave per SIMD, are too many: 32768 sites, 8 x 16^3: 17.1 against
+// 15.1, 11.6 / 10.8, 10.1 / 10.3; 8^2 x 16^2, 2: 16.7 / 14.2, 11.5 / 10.2.
+static bool few_sites(const Ctx *c, int nrhs) { return c->dirac_stage == 0 && (size_t)c->g.V * nrhs <= 16384; }
+
+template <typename T, typename S, typename O>
+static void launch_quad(Ctx *c, const void *U, const void *A, const void *in, void *out, int nrhs) {
+    const dim3 grid((c->g.V + QSITES - 1) / QSITES, nrhs);
+    const int anti = c->t_antiperiodic ? 1 : 0;
+#define QUAD(RECON)                                                                                                  \
+    dirac_quad_kernel<T, S, O, RECON><<<grid, 64, 0, c->stream>>>(c->g, (const C<T> *)U, (const C<T> *)A,            \
+                                                                  (const C<S> *)in, (C<O> *)out, anti)
+    if (c->links_su3) QUAD(true); else QUAD(false);
+#undef QUAD
+}
+
 int launch_dirac_widen(Ctx *c, int nrhs, const void *in32, void *out64, int in_prec) {
     int nwg = ((c->g.V + TPB - 1) / TPB) * nrhs;
     const int anti = c->t_antiperiodic ? 1 : 0;
@@ -323,7 +487,10 @@ int launch_dirac_widen(Ctx *c, int nrhs, const void *in32, void *out64, int in_p
     if (st < 0) return MGDD_ESHAPE;
     const bool stage = st == 1;
     const int slot = kt_begin(c);
-    if (stage && rhs_per_thread(c, true, nrhs) == 2) {   // 16^3 x 32, 4 right-hand sides: 102 -> 78 us
+    if (few_sites(c, nrhs)) {
+        if (in_prec == MGDD_F16) launch_quad<double, _Float16, double>(c, c->U64, c->A64, in32, out64, nrhs);
+        else launch_quad<double, float, double>(c, c->U64, c->A64, in32, out64, nrhs);
+    } else if (stage && rhs_per_thread(c, true, nrhs) == 2) {   // 16^3 x 32, 4 right-hand sides: 102 -> 78 us
         if (in_prec == MGDD_F16) launch_block<double, _Float16, double, 2, 1>(c, c->U64, c->A64, in32, out64, nrhs);
         else launch_block<double, float, double, 2, 1>(c, c->U64, c->A64, in32, out64, nrhs);
     } else {
@@ -367,7 +534,11 @@ int launch_dirac(Ctx *c, int prec, int nrhs, const void *in, void *out) {
         }                                                                                                             \
     } while (0)
     const int per = stage ? rhs_per_thread(c, prec == MGDD_F64, nrhs) : 1;
-    if (per > 1) {
+    if (few_sites(c, nrhs)) {
+        if (prec == MGDD_F64) launch_quad<double, double, double>(c, c->U64, c->A64, in, out, nrhs);
+        else if (prec == MGDD_F32) launch_quad<float, float, float>(c, c->U32, c->A32, in, out, nrhs);
+        else launch_quad<float, _Float16, _Float16>(c, c->U32, c->A32, in, out, nrhs);
+    } else if (per > 1) {
         if (prec == MGDD_F64) launch_block<double, double, double, 2, 1>(c, c->U64, c->A64, in, out, nrhs);
         else if (prec == MGDD_F32 && per == 2) launch_block<float, float, float, 2, 3>(c, c->U32, c->A32, in, out, nrhs);
         else if (prec == MGDD_F32) launch_block<float, float, float, 3, 2>(c, c->U32, c->A32, in, out, nrhs);

@@ -63,3 +63,39 @@ def test_solve_right_hand_sides(half):
     z1, _ = lat.solve(lat.pack(b[4:5], F64), **kw)
     assert rel(lat.unpack(z1)[0], got[4]) < 1e-12
     lat.close()
+
+
+@pytest.mark.parametrize("dims,block,unitary", [
+    ((4, 4, 4, 4), (2, 2, 2, 2), True),
+    ((8, 4, 4, 8), (4, 4, 4, 4), True),
+    ((4, 4, 8, 8), (2, 2, 4, 4), False),
+    ((8, 8, 16, 16), (4, 4, 4, 4), True),
+])
+def test_few_sites(dims, block, unitary):
+    """Up to 16384 sites of all right-hand sides the sites' hops are shared by
+    four lanes: the same bits as from the kernel for more, and the oracle's."""
+    from paper_1202_2462_amd.mgdd import F16, F32, F64, mgdd_set_kernel_options
+    if unitary:
+        op = problem(dims, seed=76, m0=0.1)
+    else:
+        op = solvers.Operator(dims, 1.01 * latgen.gauge_field(dims, 0.6, 76), 0.1, 1.2)
+    lat = lattice(op, block)
+    x = round16(latgen.gaussian_fields(dims, 3, 77))
+    want = np.stack([op.apply(v) for v in x])
+    for prec, tol in ((F64, TOL64), (F32, TOL32), (F16, 2.0 ** -10)):
+        b = lat.pack(x, prec)
+        for nrhs in (1, 2, 3):
+            say("few sites", dims, "nrhs", nrhs, "prec", prec)
+            seen = []
+            for stage in (0, -1):
+                mgdd_set_kernel_options(lat.ctx, dirac_stage=stage)
+                out = lat.field(prec, nrhs + 1)
+                out[nrhs] = 7.0
+                lat.dirac(b[:nrhs].contiguous(), out[:nrhs])
+                assert float((out[nrhs] - 7.0).abs().max()) == 0
+                seen.append(out[:nrhs])
+            assert bool((seen[0] == seen[1]).all()), (prec, nrhs)
+            got = lat.unpack(seen[0])
+            for i in range(nrhs):
+                assert rel(got[i], want[i]) < tol, (prec, nrhs, i)
+    lat.close()
