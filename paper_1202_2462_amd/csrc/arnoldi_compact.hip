@@ -45,7 +45,9 @@ struct Basis {
 
 // out[q] = sum_{g < np} part[q stride + g], q < nq <= 4 waves; one wave per q,
 // q + waves, ...; read by every thread after the barrier
-template <int WAVES>
+// U partials at a time in flight (from clamped places; 1: as they come, where
+// there are few of them)
+template <int WAVES, int U>
 __device__ inline void sum_quantities(const double2 *__restrict__ part, size_t stride, int nq, int np, double2 *out) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     double v[8];
@@ -54,12 +56,18 @@ __device__ inline void sum_quantities(const double2 *__restrict__ part, size_t s
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const int q = wave + WAVES * i;
-        if (q < nq) {
-            const double2 *p = part + q * stride;
-            for (int g = lane; g < np; g += 64) {
-                const double2 x = p[g];
-                v[2 * i] += x.x;
-                v[2 * i + 1] += x.y;
+        if (U == 1 ? q < nq : i * WAVES < nq) {
+            const double2 *p = part + (q < nq ? q : nq - 1) * stride;
+            for (int g = lane; g < np; g += 64 * U) {
+                double2 x[U];
+#pragma unroll
+                for (int u = 0; u < U; u++) x[u] = p[min(g + 64 * u, np - 1)];
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const bool in = g + 64 * u < np;
+                    v[2 * i] += in ? x[u].x : 0.0;
+                    v[2 * i + 1] += in ? x[u].y : 0.0;
+                }
             }
         }
     }
@@ -98,10 +106,11 @@ __host__ __device__ inline int chain_length(int n2) {
 // norm of the previous step ([j + 1][nin] partials, the norm last; for j = 0
 // only the norm of w).
 // Bound: reading the blocks (524 MB at 8^3 x 16 coarse sites, N = 20, 103 us at
-// the 5.1 TB/s of a large copy): 126 us there, and 11 to 20 us the pass, where
+// the 5.1 TB/s of a large copy): 126 us there, and 10 to 20 us the pass, where
 // forming each site's backward hops from its neighbours' blocks took 168 us,
 // two passes of 15 us and two sums of 11 us. At 4^3 x 8 sites the chain of
-// loads and sums decides: 12.3 and 6 to 11 us against 11.8, 7.9 and 7.9.
+// loads and sums decides: 11.7 and 5 to 7 us (6 to 11
+// with one partial sum at a time in flight) against 11.8, 7.9 and 7.9.
 __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void arnoldi_stream_kernel(
     int Vc, int N, const int *__restrict__ cnbr, const float2 *__restrict__ H, const float2 *__restrict__ w,
     const double2 *__restrict__ hin, int nin, Basis V, int j, float2 *__restrict__ vj, float2 *__restrict__ yf,
@@ -157,7 +166,7 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
             }
         }
         if (l == (int)blockIdx.x) {
-            sum_quantities<STPB / 64>(hin, (size_t)nin, j + 1, nin, coef);
+            sum_quantities<STPB / 64, 1>(hin, (size_t)nin, j + 1, nin, coef);
             const double nn = rest_norm(coef, j);
             sc = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
             if (blockIdx.x == 0) {
@@ -462,7 +471,7 @@ __global__ __launch_bounds__(PTPB) void arnoldi_vector_kernel(int n, Basis V, in
     };
     int e = (g * PTPB + (int)threadIdx.x) * 2;
     if (e < n) load(e);
-    sum_quantities<PTPB / 64>(pin + (size_t)sg * npin, (size_t)nb * npin, nk + 1, npin, coef);
+    sum_quantities<PTPB / 64, 8>(pin + (size_t)sg * npin, (size_t)nb * npin, nk + 1, npin, coef);
     const double nn = rest_norm(coef, nk), sc = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
     if (g == 0) {
         if (threadIdx.x == 0) nr[sg] = make_double2(nn, 0);
@@ -517,7 +526,7 @@ __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, cons
     int e = (g * PTPB + (int)threadIdx.x) * 2;
     if (e < n) load(e);
     if (SUB) {
-        sum_quantities<PTPB / 64>(pin + (size_t)sg * npin, (size_t)nb * npin, nk, npin, coef);
+        sum_quantities<PTPB / 64, 8>(pin + (size_t)sg * npin, (size_t)nb * npin, nk, npin, coef);
         if (g == 0 && (int)threadIdx.x < nk) hout[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
     }
     for (; e < n; e += G * PTPB * 2) {
@@ -601,7 +610,7 @@ __global__ __launch_bounds__(256) void arnoldi_last_kernel(int nk, const double2
                                                            double2 *__restrict__ h2, double2 *__restrict__ nr) {
     __shared__ double2 coef[NVMAX];
     const int sg = blockIdx.x, nb = gridDim.x;
-    sum_quantities<4>(pin + (size_t)sg * npin, (size_t)nb * npin, nk + 1, npin, coef);
+    sum_quantities<4, 8>(pin + (size_t)sg * npin, (size_t)nb * npin, nk + 1, npin, coef);
     if ((int)threadIdx.x < nk) h2[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
     if (threadIdx.x == 0) nr[sg] = make_double2(rest_norm(coef, nk), 0);
 }
