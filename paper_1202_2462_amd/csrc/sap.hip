@@ -678,7 +678,8 @@ template <> struct LaneBlock<double> {
     }
 };
 
-template <typename T, int VB, typename FV, int ESZ>
+// SHIFT: a nonzero shift (without one a sweep at 16^3 x 32 takes 64 us instead of 67)
+template <typename T, int VB, typename FV, int ESZ, bool SHIFT>
 __device__ inline void sapc_step(const Geom &g, const C<T> *__restrict__ Up, const C<T> *__restrict__ Ap,
                                  const void *__restrict__ b, void *__restrict__ z, int colour, int mr, T sre, T sim,
                                  int antiperiodic) {
@@ -810,7 +811,8 @@ __device__ inline void sapc_step(const Geom &g, const C<T> *__restrict__ Up, con
 #pragma unroll
         for (int c = 0; c < 6; c++) {
             const C<T> bs = bf.template ld_lane<true>(c, d, coff);
-            const C<T> dz = csub(csub(az[c], cscale(hs[c], (T)0.5)), cmul(shift, zc[c]));
+            C<T> dz = csub(az[c], cscale(hs[c], (T)0.5));
+            if (SHIFT) dz = csub(dz, cmul(shift, zc[c]));
             rho[c] = csub(bs, dz);
             e[c] = mk<T>((T)0, (T)0);
         }
@@ -840,7 +842,8 @@ __device__ inline void sapc_step(const Geom &g, const C<T> *__restrict__ Up, con
         Red3<T> part{0, 0, 0};
 #pragma unroll
         for (int c = 0; c < 6; c++) {
-            q[c] = csub(csub(ax[c], cscale(hs[c], (T)0.5)), cmul(shift, rho[c]));
+            q[c] = csub(ax[c], cscale(hs[c], (T)0.5));
+            if (SHIFT) q[c] = csub(q[c], cmul(shift, rho[c]));
             part.a += q[c].x * q[c].x + q[c].y * q[c].y;
             part.b += q[c].x * rho[c].x + q[c].y * rho[c].y;   // conj(q) rho
             part.c += q[c].x * rho[c].y - q[c].y * rho[c].x;
@@ -867,19 +870,19 @@ __device__ inline void sapc_step(const Geom &g, const C<T> *__restrict__ Up, con
         zf.template st_lane<true>(c, d, coff, cadd(zf.template ld_lane<true>(c, d, coff), e[c]));
 }
 
-template <int VB, typename S>
+template <int VB, typename S, bool SHIFT>
 __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(4))) void sapc_kernel(
     Geom g, const float2 *__restrict__ Up, const float2 *__restrict__ Ap, const void *__restrict__ b,
     void *__restrict__ z, int colour, int mr, float sre, float sim, int antiperiodic) {
-    sapc_step<float, VB, typename F32Store<S>::view, (int)F32Store<S>::ESZ>(g, Up, Ap, b, z, colour, mr, sre, sim,
+    sapc_step<float, VB, typename F32Store<S>::view, (int)F32Store<S>::ESZ, SHIFT>(g, Up, Ap, b, z, colour, mr, sre, sim,
                                                                            antiperiodic);
 }
 
-template <int VB>
+template <int VB, bool SHIFT>
 __global__ __launch_bounds__(2 * VB) __attribute__((amdgpu_waves_per_eu(2))) void sapc64_kernel(
     Geom g, const double2 *__restrict__ Up, const double2 *__restrict__ Ap, const void *__restrict__ b,
     void *__restrict__ z, int colour, int mr, double sre, double sim, int antiperiodic) {
-    sapc_step<double, VB, FieldView<double>, 16>(g, Up, Ap, b, z, colour, mr, sre, sim, antiperiodic);
+    sapc_step<double, VB, FieldView<double>, 16, SHIFT>(g, Up, Ap, b, z, colour, mr, sre, sim, antiperiodic);
 }
 
 }  // namespace
@@ -912,8 +915,8 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
     // fewer instructions, two lanes give twice the waves. A colour of 131072
     // sites is two waves of one-lane sites per SIMD, all that fit, and from
     // there on one lane is faster (one sweep, 4 MR steps, FP32, one / two
-    // lanes: 16^3 x 32 73 / 67 us, 16^2 x 32^2 100 / 107, 24^3 x 48 260 / 279,
-    // 32^3 x 64 653 / 772; 4^3 x 2 and 2^2 x 4^2 blocks cross at the same
+    // lanes: 16^3 x 32 73 / 64 us, 16^2 x 32^2 97 / 105, 24^3 x 48 258 / 276,
+    // 32^3 x 64 645 / 773; 4^3 x 2 and 2^2 x 4^2 blocks cross at the same
     // size). The number of right-hand sides does not enter: one of them gets
     // the same result alone and among others.
     const bool site = prec != MGDD_F64 && c->sap_lanes == 0 && lanes == 2 && g.V >= 262144 &&
@@ -922,15 +925,20 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
     // x 4^2 blocks, 3 right-hand sides, one colour: 101 us against 158 with
     // one lane per site and the links read from memory in every MR step)
     const bool two64 = prec == MGDD_F64 && c->links_su3 && 2 * ldsc <= c->lds_max;
+    const bool shifted = sre != 0 || sim != 0;
     const int slot = kt_begin(c);
     int rc = MGDD_OK;
     if (site) {
         rc = launch_sap_site(c, prec, nrhs, col, mr, sre, sim, b, z);
     } else if ((prec == MGDD_F32 || prec == MGDD_F16) && lanes == 2) {
         const int anti = c->t_antiperiodic ? 1 : 0;
-#define SAPC(VB, S)                                                                                               \
-    sapc_kernel<VB, S><<<grid, 2 * VB, ldsc, c->stream>>>(g, (const float2 *)c->U32, (const float2 *)c->A32, b, z, \
-                                                          col, mr, (float)sre, (float)sim, anti)
+#define SAPC1(VB, S, SH)                                                                                              \
+    sapc_kernel<VB, S, SH><<<grid, 2 * VB, ldsc, c->stream>>>(g, (const float2 *)c->U32, (const float2 *)c->A32, b, z, \
+                                                              col, mr, (float)sre, (float)sim, anti)
+#define SAPC(VB, S)                                                      \
+    do {                                                                 \
+        if (shifted) SAPC1(VB, S, true); else SAPC1(VB, S, false);       \
+    } while (0)
         if (prec == MGDD_F32) {
             if (g.Vb == 256) SAPC(256, float);
             else if (g.Vb == 128) SAPC(128, float);
@@ -941,14 +949,20 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
             else SAPC(64, _Float16);
         }
 #undef SAPC
+#undef SAPC1
     } else if (two64) {
         const int anti = c->t_antiperiodic ? 1 : 0;
-#define SAPC64(VB)                                                                                             \
-    sapc64_kernel<VB><<<grid, 2 * VB, 2 * ldsc, c->stream>>>(g, (const double2 *)c->U64, (const double2 *)c->A64, b, z, \
-                                                             col, mr, sre, sim, anti)
+#define SAPC641(VB, SH)                                                                                              \
+    sapc64_kernel<VB, SH><<<grid, 2 * VB, 2 * ldsc, c->stream>>>(g, (const double2 *)c->U64, (const double2 *)c->A64, \
+                                                                 b, z, col, mr, sre, sim, anti)
+#define SAPC64(VB)                                                  \
+    do {                                                            \
+        if (shifted) SAPC641(VB, true); else SAPC641(VB, false);    \
+    } while (0)
         if (g.Vb == 256) SAPC64(256);
         else if (g.Vb == 128) SAPC64(128);
         else SAPC64(64);
+#undef SAPC641
 #undef SAPC64
     } else if (prec == MGDD_F64) {
         sap_colour_kernel<double><<<grid, g.Vb, lds, c->stream>>>(g, (const double2 *)c->U64, (const double2 *)c->A64,
