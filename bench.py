@@ -553,7 +553,7 @@ def main():
         achieved = bytes_launch / t_launch / 1e9
         tps = counter_traffic(TRAFFIC_FILE, SAP_SOURCES) if big else None
         lines["sap"] = (sap_ms, {
-            "bound": "hbm", "kernel": "sapc_kernel<256> (FP32 Schwarz colour step, 4 MR steps)",
+            "bound": "hbm", "kernel": "sap_site_kernel<256, float> (FP32 Schwarz colour step, 4 MR steps)",
             "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
             "traffic": None if tps is None else tps * units_launch,
             "launches": sap_n, "us_per_launch": t_launch * 1e6, "total_ms_in_timed_steps": sap_ms,
@@ -570,8 +570,8 @@ def main():
         tpc = counter_traffic(COARSE_TRAFFIC_FILE, COARSE_SOURCES) if big else None
         n2 = 2 * bench.N
         lines["coarse"] = (c_ms, {
-            "bound": "hbm", "kernel": "arnoldi_apply_kernel<float, true> (coarse GMRES step on the compact FP32 "
-                                      "D_c: self block and forward hops stored, backward hops from "
+            "bound": "hbm", "kernel": "arnoldi_stream_kernel (coarse GMRES step on the compact FP32 D_c: self block "
+                                      "and forward hops stored and read once, backward hops from "
                                       "gamma5^c-hermiticity)",
             "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
             "traffic": None if tpc is None else tpc * units_launch,

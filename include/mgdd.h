@@ -561,9 +561,9 @@ int mgdd_timing_enable(mgdd_ctx *ctx, int on);
  * right-hand side read and written once. Per site: an FP64 apply of n fields
  * 960 + 384 n (1152 + 384 n with full links), of n FP32 fields 960 + 288 n,
  * of n half fields 960 + 240 n; FP32 480 + 192 n (576 + 192 n), half
- * 480 + 96 n; per site of a Schwarz colour step 480 + 288 n (FP32, two lanes
- * per site), 576 + 288 n (FP32, 1 or 4 lanes), 480 + 144 n (half), 1152 + 576 n
- * (FP64); per coarse site of a coarse step with N test vectors and j earlier
+ * 480 + 96 n; per site of a Schwarz colour step 480 + 288 n (FP32, links
+ * as two rows), 576 + 288 n (FP32, whole links), 480 + 144 n (half), 960 + 576 n
+ * (FP64, links as two rows), 1152 + 576 n (FP64); per coarse site of a coarse step with N test vectors and j earlier
  * basis vectors 5 (2N)^2 blocks (the compact FP32 D_c, else 9) plus
  * (3 + j) 2N values per right-hand side. reset: nonzero to zero these totals
  * afterwards. Errors: MGDD_EINVAL (bad kernel or precision). */

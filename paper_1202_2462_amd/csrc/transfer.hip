@@ -599,14 +599,15 @@ int transfer_setup(Ctx *c, const int *agg, int N) {
     return MGDD_OK;
 }
 
-// device memory, aligned for 16-byte loads
+// memory of the current device, aligned for 16-byte loads
 static bool kernel_readable(const void *p) {
     hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && !((uintptr_t)p & 15);
+    return at.type == hipMemoryTypeDevice && at.device == dev && !((uintptr_t)p & 15);
 }
 
 int launch_build_P(Ctx *c, const void *tv64) {
