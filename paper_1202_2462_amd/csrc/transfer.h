@@ -47,6 +47,21 @@ int transfer_setup(Ctx *c, const int *agg, int N);
 // P from N FP64 fine fields (device layout); FP32 copy made too. MGDD_ERANK if rank deficient.
 int launch_build_P(Ctx *c, const void *tv64);
 int launch_restrict(Ctx *c, int prec, int nrhs, const void *fine, void *coarse);
+
+// How a restriction divides the N test vectors of an (aggregate, chirality)
+// pair: `parts` workgroups of `per` consecutive ones, the last with what is
+// left, none with nothing (the kernel loads a part's first column of P at once).
+// Few workgroups (one per pair and group of right-hand sides): up to 4 parts,
+// so that the launch fills the chip.
+struct RestrictSplit {
+    int parts, per;
+};
+inline RestrictSplit restrict_split(int N, size_t workgroups) {
+    int ks = 1;
+    while (ks < 4 && ks < N && workgroups * ks < 1024) ks *= 2;
+    const int per = (N + ks - 1) / ks;
+    return {(N + per - 1) / per, per};
+}
 int launch_prolong(Ctx *c, int prec, int nrhs, const void *coarse, void *fine);
 int launch_coarse_build(Ctx *c);
 int launch_coarse_apply(Ctx *c, int prec, int nrhs, const void *in, void *out);

@@ -245,13 +245,14 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(2))) void b
 template <typename T, typename SP, typename SF, int R>
 __global__ __launch_bounds__(TPB) void restrict_kernel(int V, int Va, int N, const int *__restrict__ agg_sites,
                                                              const C<SP> *__restrict__ P, const C<SF> *__restrict__ f,
-                                                             C<T> *__restrict__ out, int Vc, int nrhs, int ks) {
+                                                             C<T> *__restrict__ out, int Vc, int nrhs, int ks,
+                                                             int kper) {
     extern __shared__ unsigned char smem[];
     constexpr int NS = (2 * R + 7) / 8 * 8;   // sums per k, rounded up to eights
     T *red = (T *)smem;                       // [waves][kper][NS]
     const int wg = xcd_block(gridDim.x), r0 = blockIdx.y * R;
     const int part = wg % ks, ac = wg / ks, chi = ac & 1, a = ac >> 1;
-    const int kper = (N + ks - 1) / ks, kb = part * kper, ke = kb + kper < N ? kb + kper : N;
+    const int kb = part * kper, ke = kb + kper < N ? kb + kper : N;
     const int *sites = agg_sites + (size_t)a * Va;
     const size_t fs = (size_t)12 * V;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
@@ -683,17 +684,14 @@ int launch_restrict(Ctx *c, int prec, int nrhs, const void *fine, void *coarse) 
     const Level1 &L1 = c->c;
     const void *P = prec == MGDD_F64 ? L1.P64 : prec == MGDD_F32 ? L1.P32 : L1.P16;
     const int R = rhs_per_thread(prec, nrhs), groups = (nrhs + R - 1) / R;
-    // few (aggregate, chirality) pairs: split the test vectors over up to 4
-    // workgroups each, so that the launch fills the chip
-    int ks = 1;
-    while (ks < 4 && ks < L1.N && (size_t)L1.Vc * 2 * groups * ks < 1024) ks *= 2;
-    const int kper = (L1.N + ks - 1) / ks, ns = (2 * R + 7) / 8 * 8;
+    const RestrictSplit split = restrict_split(L1.N, (size_t)L1.Vc * 2 * groups);
+    const int ks = split.parts, kper = split.per, ns = (2 * R + 7) / 8 * 8;
     const unsigned threads = L1.Va >= TPB ? TPB : (unsigned)((L1.Va + 63) / 64 * 64);
     const size_t lds = (size_t)(threads / 64) * kper * ns * (prec == MGDD_F64 ? 8 : 4);
     const dim3 grid((unsigned)(L1.Vc * 2 * ks), (unsigned)groups);
 #define RESTRICT(T, SP, SF, RR)                                                                          \
     restrict_kernel<T, SP, SF, RR><<<grid, threads, lds, c->stream>>>(                                   \
-        c->g.V, L1.Va, L1.N, L1.agg_sites, (const C<SP> *)P, (const C<SF> *)fine, (C<T> *)coarse, L1.Vc, nrhs, ks)
+        c->g.V, L1.Va, L1.N, L1.agg_sites, (const C<SP> *)P, (const C<SF> *)fine, (C<T> *)coarse, L1.Vc, nrhs, ks, kper)
     MULTI(RESTRICT);
 #undef RESTRICT
     return hip_check(c, hipGetLastError(), "restrict kernel");
