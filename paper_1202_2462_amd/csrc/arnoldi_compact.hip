@@ -19,11 +19,12 @@
 //   pass:   y = yf + sum t - V h1 (in double), sums of <v_k, y> and |y|^2.
 // With |y|^2 = |y - V h2|^2 + |h2|^2 for the orthonormal V no third kernel has
 // to form the norm. Several right-hand sides take four: v_j, the products on
-// the matrix cores, the sums of <v_k, yf + sum t>, the first projection.
-// Both forms do the same arithmetic in FP32, operation by operation, so that a
-// right-hand side gets the same result alone and among others: a 16x16x4 FP32
+// the matrix cores, the sums of <v_k, D_c v_j>, the pass.
+// Both forms do the same arithmetic, operation by operation, so that a
+// right-hand side gets the same bits alone and among others: a 16x16x4 FP32
 // MFMA is the chain of fused multiply-adds over its four summation indices in
-// ascending order (checked on the card), and the stream kernel sums in fours.
+// ascending order (checked on the card), and the stream kernel sums in fours;
+// the sums in double take the same products in the same order and partition.
 #include "lanes.h"
 #include "stencil.h"
 #include "transfer.h"
@@ -77,12 +78,19 @@ __device__ inline void sum_quantities(const double2 *__restrict__ part, size_t s
     __syncthreads();
 }
 
-// |y - V h2|^2 from |y|^2 (the last quantity) and h2
+// |y - V h2|^2 from |y|^2 (the last quantity) and h2; the multiply-adds are
+// spelt out, so that every kernel that forms it gets the same bits
 __device__ inline double rest_norm(const double2 *coef, int nk) {
     double nn = coef[nk].x;
 #pragma unroll 1
-    for (int k = 0; k < nk; k++) nn -= coef[k].x * coef[k].x + coef[k].y * coef[k].y;
+    for (int k = 0; k < nk; k++) nn = fma(-coef[k].y, coef[k].y, fma(-coef[k].x, coef[k].x, nn));
     return nn;
+}
+
+// acc += conj(v) u of two entries
+__device__ inline void add_products(double2 &acc, v4f v, v4f u) {
+    cfmac(acc, make_double2((double)v[0], (double)v[1]), make_double2((double)u[0], (double)u[1]));
+    cfmac(acc, make_double2((double)v[2], (double)v[3]), make_double2((double)u[2], (double)u[3]));
 }
 
 // Both products sum in batches of four: a batch of the row sums is four
@@ -274,9 +282,9 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
             const int k = wave + 4 * i;
             if (k <= j)
 #pragma unroll 2
-                for (int e = lane; e < n5; e += 64) {
-                    const float2 v = vs[k * n5 + e], u = us[e];
-                    cfmac(acc[i], make_double2((double)v.x, (double)v.y), make_double2((double)u.x, (double)u.y));
+                for (int e = 2 * lane; e < n5; e += 128) {
+                    const v4f v = *(const v4f *)(vs + k * n5 + e), u = *(const v4f *)(us + e);
+                    add_products(acc[i], v, u);
                 }
         }
         __syncthreads();
@@ -301,8 +309,8 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
 // B[k][j] in lane j + 16 k, result register v of lane l holds row 4 (l / 16) +
 // v of column l % 16. One MFMA is one batch of the stream kernel's sums.
 // Bound: the latency of each block's way through LDS (matrix cores 34 %, vector
-// units 28 % busy). 6^3 x 12 coarse sites, N = 24, 12 right-hand sides: 169 us,
-// and 48 to 117 us the other three kernels; reading the blocks once per
+// units 28 % busy). 6^3 x 12 coarse sites, N = 24, 12 right-hand sides: 161 us,
+// and 46 to 181 us the other three kernels; reading the blocks once per
 // right-hand side took 725 us and two passes of 92 us.
 __device__ inline v4f mma(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -491,14 +499,82 @@ __global__ __launch_bounds__(PTPB) void arnoldi_vector_kernel(int n, Basis V, in
     }
 }
 
-// ---------------------------------------------------------------- passes over the basis
+// The sums of <v_k, D_c v_j>, k <= j, for several right-hand sides, from yf and t:
+// the products, the workgroups' sites and the order of the stream kernel, so
+// that both give the same bits. A lane holds Q pairs of a site's 5 n2 entries
+// (128 (Q - 1) < 5 n2 <= 128 Q) for K basis vectors, the next site's in flight.
+// part: [k][segment][workgroup]. Grid (G, nb, ceil((j + 1) / 4 K)), G as the
+// stream kernel's. Bound: the basis, read at a site and its four forward
+// neighbours, from L2. 12 right-hand sides, steps 1 to 12, 6^3 x 12 coarse sites,
+// N = 24: 16 to 83 us (K = 1: 15 to 85, 4: 20 to 75), 8^3 x 16, N = 20: 39 to
+// 269. Sums of <v_k, yf + sum t>, which read the basis once but in another order,
+// took 13 to 39 and 31 to 98 us.
+template <int Q, int K>
+__global__ __launch_bounds__(STPB) void arnoldi_dots_kernel(int Vc, int n2, const int *__restrict__ cnbr, Basis V, int j,
+                                                            const float2 *__restrict__ yf, const float2 *__restrict__ t,
+                                                            double2 *__restrict__ part) {
+    const int k0 = 4 * K * blockIdx.z + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (k0 > j) return;
+    const int sg = blockIdx.y, nb = gridDim.y, n5 = 5 * n2;
+    const size_t so = (size_t)sg * Vc * n2;
+    const float2 *vk[K];
+#pragma unroll
+    for (int i = 0; i < K; i++) vk[i] = V.p[k0 + 4 * i <= j ? k0 + 4 * i : j] + so;
+    // the lane's entries of a site: past the end the last ones, as 0
+    int dir[Q], in[Q], ent[Q];
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        const int e = 2 * lane + 128 * q < n5 ? 2 * lane + 128 * q : n5 - 2, dd = e / n2;
+        dir[q] = dd ? 2 * dd - 1 : 0;
+        in[q] = e - dd * n2;
+        ent[q] = e - n2;   // of t, or below 0 of yf
+    }
+    int at[Q];
+    v4f u[Q];
+    auto fetch = [&](int l) {
+        const int a = __builtin_amdgcn_readfirstlane(xcd_remap(l, Vc));
+        const float2 *ys = yf + so + (size_t)a * n2 + n2, *ts = t + 4 * (so + (size_t)a * n2);
+#pragma unroll
+        for (int q = 0; q < Q; q++) at[q] = cnbr[a * 9 + dir[q]];
+#pragma unroll
+        for (int q = 0; q < Q; q++) u[q] = *(const v4f *)((ent[q] < 0 ? ys : ts) + ent[q]);
+    };
+    fetch(blockIdx.x);
+    double2 acc[K];
+#pragma unroll
+    for (int i = 0; i < K; i++) acc[i] = make_double2(0, 0);
+    for (int l = blockIdx.x; l < Vc; l += gridDim.x) {
+        v4f v[K][Q], x[Q];
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+#pragma unroll
+            for (int i = 0; i < K; i++) v[i][q] = *(const v4f *)(vk[i] + (size_t)at[q] * n2 + in[q]);
+#pragma unroll
+        for (int q = 0; q < Q; q++) x[q] = 2 * lane + 128 * q < n5 ? u[q] : (v4f){0, 0, 0, 0};
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(l + (int)gridDim.x < Vc ? l + (int)gridDim.x : l);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+#pragma unroll
+            for (int i = 0; i < K; i++) add_products(acc[i], v[i][q], x[q]);
+    }
+#pragma unroll
+    for (int i = 0; i < K; i++) {
+        const int k = k0 + 4 * i;
+        const double re = wave_sum1(acc[i].x), im = wave_sum1(acc[i].y);
+        if (lane == 0 && k <= j) part[((size_t)k * nb + sg) * gridDim.x + blockIdx.x] = make_double2(re, im);
+    }
+}
+
+// ---------------------------------------------------------------- the pass over the basis
 //
-// z = yf + sum_mu t_mu(a - mu) in double [SUB: - sum_{k < nk} coef_k v_k, coef
+// z = yf + sum_mu t_mu(a - mu) in double - sum_{k < nk} coef_k v_k, coef
 // summed from pin (npin partials each), stored in y = yf, in FP32, and coef by
-// workgroup 0 in hout[k nb + segment]]; then the sums of <v_k, z> (k < nk) and,
-// with SUB, of |z|^2 (as quantity nk) of each workgroup into pout
+// workgroup 0 in hout[k nb + segment]; then the sums of <v_k, z> (k < nk) and of
+// |z|^2 (as quantity nk) of each workgroup into pout
 // [quantity][segment][workgroup]. Grid (G, nb).
-template <int NV, bool SUB>
+template <int NV>
 __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, const int *__restrict__ cnbr, Basis V,
                                                             int nk, const double2 *__restrict__ pin, int npin,
                                                             float2 *__restrict__ y, const float2 *__restrict__ t,
@@ -525,10 +601,8 @@ __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, cons
     for (int q = 0; q < NQ; q++) acc[q] = 0;
     int e = (g * PTPB + (int)threadIdx.x) * 2;
     if (e < n) load(e);
-    if (SUB) {
-        sum_quantities<PTPB / 64, 8>(pin + (size_t)sg * npin, (size_t)nb * npin, nk, npin, coef);
-        if (g == 0 && (int)threadIdx.x < nk) hout[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
-    }
+    sum_quantities<PTPB / 64, 8>(pin + (size_t)sg * npin, (size_t)nb * npin, nk, npin, coef);
+    if (g == 0 && (int)threadIdx.x < nk) hout[(size_t)threadIdx.x * nb + sg] = coef[threadIdx.x];
     for (; e < n; e += G * PTPB * 2) {
         double2 y0 = make_double2((double)yv[0], (double)yv[1]), y1 = make_double2((double)yv[2], (double)yv[3]);
 #pragma unroll
@@ -536,22 +610,20 @@ __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, cons
             y0 = cadd(y0, make_double2((double)tv[mu][0], (double)tv[mu][1]));
             y1 = cadd(y1, make_double2((double)tv[mu][2], (double)tv[mu][3]));
         }
-        if (SUB) {
 #pragma unroll
-            for (int k = 0; k < NV; k++)
-                if (k < nk) {
-                    const double2 h = cneg(coef[k]);
-                    cfma(y0, h, make_double2((double)v[k][0], (double)v[k][1]));
-                    cfma(y1, h, make_double2((double)v[k][2], (double)v[k][3]));
-                }
-            yv = (v4f){(float)y0.x, (float)y0.y, (float)y1.x, (float)y1.y};
-            *(v4f *)(y + so + e) = yv;
-            y0 = make_double2((double)yv[0], (double)yv[1]);
-            y1 = make_double2((double)yv[2], (double)yv[3]);
-            // the products below widen v again: kept in double it would not fit the registers
+        for (int k = 0; k < NV; k++)
+            if (k < nk) {
+                const double2 h = cneg(coef[k]);
+                cfma(y0, h, make_double2((double)v[k][0], (double)v[k][1]));
+                cfma(y1, h, make_double2((double)v[k][2], (double)v[k][3]));
+            }
+        yv = (v4f){(float)y0.x, (float)y0.y, (float)y1.x, (float)y1.y};
+        *(v4f *)(y + so + e) = yv;
+        y0 = make_double2((double)yv[0], (double)yv[1]);
+        y1 = make_double2((double)yv[2], (double)yv[3]);
+        // the products below widen v again: kept in double it would not fit the registers
 #pragma unroll
-            for (int k = 0; k < NV; k++) asm volatile("" : "+v"(v[k]));
-        }
+        for (int k = 0; k < NV; k++) asm volatile("" : "+v"(v[k]));
 #pragma unroll
         for (int k = 0; k < NV; k++)
             if (k < nk) {
@@ -561,21 +633,20 @@ __global__ __launch_bounds__(PTPB) void arnoldi_pass_kernel(int Vc, int n2, cons
                 acc[2 * k] = d.x;
                 acc[2 * k + 1] = d.y;
             }
-        if (SUB) acc[2 * NV] += (y0.x * y0.x + y0.y * y0.y) + (y1.x * y1.x + y1.y * y1.y);
+        acc[2 * NV] += (y0.x * y0.x + y0.y * y0.y) + (y1.x * y1.x + y1.y * y1.y);
         if (e + G * PTPB * 2 < n) load(e + G * PTPB * 2);
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int q = 0; q < NQ; q += 8)
-        if (q == 2 * NV ? SUB : q < 2 * nk) {
+        if (q == 2 * NV || q < 2 * nk) {
             const double s = wave_sum8(acc + q);
             if (!(lane & 7)) red[wave][q + (lane >> 3)] = s;
         }
     __syncthreads();
-    const int nq = nk + (SUB ? 1 : 0);
-    if ((int)threadIdx.x < nq) {
+    if ((int)threadIdx.x <= nk) {
         const int q = threadIdx.x;
-        const bool norm = SUB && q == nk;
+        const bool norm = q == nk;
         double re = 0, im = 0;
         for (int u = 0; u < PTPB / 64; u++) {
             re += red[u][norm ? 2 * NV : 2 * q];
@@ -620,6 +691,9 @@ int pass_grid(size_t n) {
     return (int)(g < 1 ? 1 : g > PGRID ? PGRID : g);
 }
 
+// the most workgroups of a stream kernel
+int stream_most(int Vc) { return Vc < 768 ? Vc : 768; }
+
 size_t stream_lds(int n2, int j) {
     const int NR = row_groups(n2), M = chain_length(n2), CG = (5 * NR + M - 1) / M;
     return 8 * ((size_t)(j + 2) * 5 * n2 + (size_t)CG * n2 + (size_t)4 * n2 * NR);
@@ -638,8 +712,8 @@ int stream_grid(int Vc, int n2, int j) {
 
 size_t compact_arnoldi_scratch(const StencilOp &op, int m, int nb) {
     const size_t n = (size_t)op.V * 2 * op.N;
-    // t, the sums of the stream kernel (768 workgroups at most), those of two passes
-    return 4 * n * nb * 8 + ((size_t)(m + 2) * 768 + 2 * (size_t)(m + 2) * nb * pass_grid(n)) * 16 + 1024;
+    // t, the sums of the products and those of the pass
+    return 4 * n * nb * 8 + (size_t)(m + 2) * nb * (stream_most(op.V) + pass_grid(n)) * 16 + 1024;
 }
 
 int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const void *b, void *const *V, void *work0,
@@ -650,22 +724,13 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
     if (m + 1 > NVMAX) return fail(c, MGDD_EINVAL, "too many coarse GMRES steps for the fused Arnoldi kernels");
     float2 *t = (float2 *)scratch;
     double2 *part1 = (double2 *)(((uintptr_t)(t + 4 * n * nb) + 255) & ~(uintptr_t)255);
-    double2 *part2 = part1 + (size_t)(m + 2) * 768;
-    double2 *part3 = part2 + (size_t)(m + 2) * nb * G;
+    double2 *part3 = part1 + (size_t)(m + 2) * nb * stream_most(Vc);
     const dim3 grid(G, nb);
     const float2 *H = (const float2 *)op.H32;
     void *work[2] = {work0, work1};
     const void *w = b;
     arnoldi_norm_kernel<<<grid, PTPB, 0, c->stream>>>((int)n, (const float2 *)b, part3);
-#define PASS_NV(NV, SUB, PIN, NPIN, POUT, HOUT)                                                             \
-    arnoldi_pass_kernel<NV, SUB><<<grid, PTPB, 0, c->stream>>>(Vc, n2, op.nbr, vl, j + 1, PIN, NPIN, y, t, POUT, HOUT)
-#define PASS(SUB, PIN, NPIN, POUT, HOUT)                              \
-    do {                                                              \
-        if (j < 4) PASS_NV(4, SUB, PIN, NPIN, POUT, HOUT);            \
-        else if (j < 8) PASS_NV(8, SUB, PIN, NPIN, POUT, HOUT);       \
-        else if (j < 12) PASS_NV(12, SUB, PIN, NPIN, POUT, HOUT);     \
-        else PASS_NV(16, SUB, PIN, NPIN, POUT, HOUT);                 \
-    } while (0)
+#define PASS(NV) arnoldi_pass_kernel<NV><<<grid, PTPB, 0, c->stream>>>(Vc, n2, op.nbr, vl, j + 1, part1, gs, y, t, part3, h1)
     int rc = MGDD_OK;
     for (int j = 0; j < m && !rc; j++) {
         Basis vl{};
@@ -676,14 +741,13 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
         // right-hand side w read, y and v_j written and the j earlier basis vectors read
         const double abytes = (double)Vc * (5.0 * n2 * n2 * 8 + nb * (3.0 + j) * n2 * 8);
         double2 *h2p = H2 + (size_t)(j ? j - 1 : 0) * (m + 1) * nb, *nrj = NR + (size_t)j * nb;
+        const int gs = stream_grid(Vc, n2, j);
         int slot;
         if (nb == 1) {
-            const int gs = stream_grid(Vc, n2, j);
             slot = kt_begin(c);
             arnoldi_stream_kernel<<<gs, STPB, stream_lds(n2, j), c->stream>>>(
                 Vc, N, op.nbr, H, (const float2 *)w, part3, G, vl, j, vj, y, t, part1, h2p, nrj);
             kt_end(c, slot, KF_COARSE, MGDD_F32, (double)Vc, abytes);
-            PASS(true, part1, gs, part3, h1);
         } else {
 #define VECTOR(NV)                                                                                                    \
     arnoldi_vector_kernel<NV><<<grid, PTPB, 0, c->stream>>>((int)n, vl, j, part3, G, (const float2 *)w, vj, h2p, nrj)
@@ -696,14 +760,21 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
             arnoldi_mfma_kernel<<<dim3(Vc, (nb + 15) / 16), 128 * ((n2 + 15) / 16), lds, c->stream>>>(Vc, N, nb, op.nbr,
                                                                                                     H, vj, y, t);
             kt_end(c, slot, KF_COARSE, MGDD_F32, (double)Vc * nb, abytes);
-            PASS(false, nullptr, 0, part2, nullptr);
-            PASS(true, part2, G, part3, h1);
+#define DOTS(Q)                                                                                                  \
+    arnoldi_dots_kernel<Q, 2><<<dim3(gs, nb, (j + 8) / 8), STPB, 0, c->stream>>>(Vc, n2, op.nbr, vl, j, y, t, part1)
+            if (n2 <= 25) DOTS(1);
+            else if (n2 <= 51) DOTS(2);
+            else DOTS(3);
+#undef DOTS
         }
+        if (j < 4) PASS(4);
+        else if (j < 8) PASS(8);
+        else if (j < 12) PASS(12);
+        else PASS(16);
         rc = hip_check(c, hipGetLastError(), "arnoldi");
         w = y;
     }
 #undef PASS
-#undef PASS_NV
     if (!rc) {
         arnoldi_last_kernel<<<nb, 256, 0, c->stream>>>(m, part3, G, H2 + (size_t)(m - 1) * (m + 1) * nb,
                                                        NR + (size_t)m * nb);

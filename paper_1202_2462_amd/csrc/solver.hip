@@ -288,7 +288,22 @@ int coarse_gmres(Ctx *c, int p, int m, int nb, const void *b, void *x, Arena &A,
 // on a non-finite result).
 int stencil_gmres(Ctx *c, const StencilOp &op, int p, int m, int nb, const void *b, void *x, Arena &A, int *status) {
     const size_t n = (size_t)op.V * 2 * op.N, cs = csize(p);
-    const size_t mark = A.off;
+    const size_t mark = A.off, room = A.cap - A.off;
+    // the steps on a compact D_c take four more vectors: in a caller's fixed
+    // workspace without room for those of all right-hand sides these go in the
+    // fewest groups that it holds, each with the result it has alone (one whose
+    // own vectors do not fit takes the general steps below)
+    if (nb > 1 && compact_scratch(op, p, m, nb) && stencil_gmres_bytes(op, p, m, nb) > room &&
+        stencil_gmres_bytes(op, p, m, 1) <= room) {
+        int groups = 2;
+        while (stencil_gmres_bytes(op, p, m, (nb + groups - 1) / groups) > room) groups++;
+        const int per = (nb + groups - 1) / groups;
+        int rc = MGDD_OK;
+        for (int s = 0; s < nb && !rc; s += per)
+            rc = stencil_gmres(c, op, p, m, std::min(per, nb - s), (const char *)b + s * n * cs, (char *)x + s * n * cs, A,
+                               status);
+        return rc;
+    }
     std::vector<void *> V(m + 1);
     for (int i = 0; i <= m; i++) V[i] = A.take(n * nb * cs);
     void *w = A.take(n * nb * cs);
@@ -301,8 +316,6 @@ int stencil_gmres(Ctx *c, const StencilOp &op, int p, int m, int nb, const void 
     int rc = MGDD_OK;
     if (m <= ARNOLDI_FUSED_MAX_STEPS) {
         void *w2 = A.take(n * nb * cs);
-        // the steps on a compact D_c take four more vectors; a caller's fixed
-        // workspace that holds the others but not these gets the general ones
         const size_t compact = compact_scratch(op, p, m, nb);
         const bool fits = compact && A.off + compact + 256 <= A.cap;
         void *scr = A.take(fits ? compact : coarse_arnoldi_scratch(op, m, nb));
