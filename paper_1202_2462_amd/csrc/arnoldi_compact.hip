@@ -10,15 +10,15 @@
 // coarse site at N = 20, and twice the traffic from L2).
 //
 // Gram-Schmidt is classical with one re-orthogonalisation, coefficients and
-// sums in double, every sum in a fixed order. One right-hand side takes two
-// kernels a step (they are short, so their number counts):
+// sums in double, every sum in a fixed order. One right-hand side or a few take
+// two kernels a step (they are short, so their number counts):
 //   stream: v_j = (y - V h2) / |.| at a and its forward neighbours, with h2
 //           and the norm from the previous step's sums (the second pass of
 //           step j - 1), then the products with the blocks of a, and the sums
 //           of <v_k, D_c v_j>, taken with yf at a and with t_mu at a + mu;
 //   pass:   y = yf + sum t - V h1 (in double), sums of <v_k, y> and |y|^2.
 // With |y|^2 = |y - V h2|^2 + |h2|^2 for the orthonormal V no third kernel has
-// to form the norm. Several right-hand sides take four: v_j, the products on
+// to form the norm. More right-hand sides take four: v_j, the products on
 // the matrix cores, the sums of <v_k, D_c v_j>, the pass.
 // Both forms do the same arithmetic, operation by operation, so that a
 // right-hand side gets the same bits alone and among others: a 16x16x4 FP32
@@ -104,23 +104,23 @@ __host__ __device__ inline int chain_length(int n2) {
     return (5 * nb4 + groups - 1) / groups;
 }
 
-// ---------------------------------------------------------------- one right-hand side
+// ---------------------------------------------------------------- one right-hand side or a few
 //
-// One workgroup per coarse site, the workgroups of the grid taking the sites
-// in turn. Thread (cg, rg) takes the rows 4 rg .. 4 rg + 3 of chain cg of the
-// column batches of the site's 5 blocks (column-major): a column of 4 rows is
-// 32 contiguous bytes, read once and used for both products; the row sums are
-// added over cg, the column sums over rg, through LDS. hin: h2 and the squared
-// norm of the previous step ([j + 1][nin] partials, the norm last; for j = 0
-// only the norm of w).
+// One workgroup per coarse site and right-hand side, the G workgroups of a
+// right-hand side taking the sites in turn. Thread (cg, rg) takes the rows
+// 4 rg .. 4 rg + 3 of chain cg of the column batches of the site's 5 blocks
+// (column-major): a column of 4 rows is 32 contiguous bytes, read once and used
+// for both products; the row sums are added over cg, the column sums over rg,
+// through LDS. hin: h2 and the squared norm of the previous step ([j + 1][nb][nin]
+// partials, the norm last; for j = 0 only the norm of w).
 // Bound: reading the blocks (524 MB at 8^3 x 16 coarse sites, N = 20, 103 us at
 // the 5.1 TB/s of a large copy): 126 us there, and 10 to 20 us the pass, where
 // forming each site's backward hops from its neighbours' blocks took 168 us,
 // two passes of 15 us and two sums of 11 us. At 4^3 x 8 sites the chain of
-// loads and sums decides: 11.7 and 5 to 7 us (6 to 11
-// with one partial sum at a time in flight) against 11.8, 7.9 and 7.9.
+// loads and sums decides: 11.7 and 5 to 7 us (6 to 11 with one partial sum at a
+// time in flight) against 11.8, 7.9 and 7.9.
 __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void arnoldi_stream_kernel(
-    int Vc, int N, const int *__restrict__ cnbr, const float2 *__restrict__ H, const float2 *__restrict__ w,
+    int Vc, int N, int nb, const int *__restrict__ cnbr, const float2 *__restrict__ H, const float2 *__restrict__ w,
     const double2 *__restrict__ hin, int nin, Basis V, int j, float2 *__restrict__ vj, float2 *__restrict__ yf,
     float2 *__restrict__ t, double2 *__restrict__ part, double2 *__restrict__ h2, double2 *__restrict__ nr) {
     extern __shared__ float2 sm[];
@@ -134,6 +134,20 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
     const int cg = tid / NR, rg = tid - cg * NR, row = 4 * rg;
     const bool active = cg < CG;
     const size_t blk = (size_t)n2 * n2;
+    // workgroup g of G and right-hand side sg: the right-hand sides of a g one
+    // after the other on its XCD
+    const int G = gridDim.x / nb, full = G & ~7;
+    int g = blockIdx.x, sg = 0;
+    if (nb > 1) {
+        const int r = blockIdx.x - full * nb;
+        g = r < 0 ? (int)(blockIdx.x / 8 / nb) * 8 + (int)(blockIdx.x & 7) : full + r / nb;
+        sg = r < 0 ? (int)(blockIdx.x / 8 % nb) : r % nb;
+    }
+    const size_t so = (size_t)sg * Vc * n2;
+    w += so;
+    vj += so;
+    yf += so;
+    t += 4 * so;
     // the four columns of batch m (4 rows each) through a buffer resource over
     // the site's blocks: past the end reads as 0 (rows past n2 and columns past
     // a block, where n2 is no multiple of 4, are others that the sums below
@@ -151,13 +165,13 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
     };
     // in flight while the sums are taken and v_j is formed
     v4f f[4][2];
-    columns(__builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, Vc)), cg * M, f);
+    columns(__builtin_amdgcn_readfirstlane(xcd_remap(g, Vc)), cg * M, f);
     const int wave = tid >> 6, lane = tid & 63;
     double sc = 0;
     double2 acc[4];
 #pragma unroll
     for (int i = 0; i < 4; i++) acc[i] = make_double2(0, 0);
-    for (int l = blockIdx.x; l < Vc; l += gridDim.x) {
+    for (int l = g; l < Vc; l += G) {
         const int a = __builtin_amdgcn_readfirstlane(xcd_remap(l, Vc));
         // the vectors at a and its forward neighbours (5 n2 <= 320 entries), loaded
         // before the coefficients are summed for the first site
@@ -170,16 +184,16 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
                 at[u] = (size_t)cnbr[a * 9 + (dd ? 2 * dd - 1 : 0)] * n2 + i;
                 wv[u] = w[at[u]];
 #pragma unroll 4
-                for (int k = 0; k < j; k++) vs[k * n5 + e] = V.p[k][at[u]];
+                for (int k = 0; k < j; k++) vs[k * n5 + e] = V.p[k][so + at[u]];
             }
         }
-        if (l == (int)blockIdx.x) {
-            sum_quantities<STPB / 64, 1>(hin, (size_t)nin, j + 1, nin, coef);
+        if (l == g) {
+            sum_quantities<STPB / 64, 1>(hin + (size_t)sg * nin, (size_t)nb * nin, j + 1, nin, coef);
             const double nn = rest_norm(coef, j);
             sc = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
-            if (blockIdx.x == 0) {
-                if (tid == 0) nr[0] = make_double2(nn, 0);
-                if (tid < j) h2[tid] = coef[tid];
+            if (g == 0) {
+                if (tid == 0) nr[sg] = make_double2(nn, 0);
+                if (tid < j) h2[(size_t)tid * nb + sg] = coef[tid];
             }
         }
 #pragma unroll
@@ -253,8 +267,8 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
             for (int r = 0; r < 4; r++)
                 if (row + r < n2) yp[cg * n2 + row + r] = y4[r];
         }
-        if (l + (int)gridDim.x < Vc)   // the next site's
-            columns(__builtin_amdgcn_readfirstlane(xcd_remap(l + gridDim.x, Vc)), cg * M, f);
+        if (l + G < Vc)   // the next site's
+            columns(__builtin_amdgcn_readfirstlane(xcd_remap(l + G, Vc)), cg * M, f);
         __syncthreads();
         // four lanes a row of yf, one thread an entry of t (4 n2 <= 256 of each)
         if (tid < 4 * n2) {
@@ -293,7 +307,7 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
     const double s = wave_sum8(v);
     const int k = wave + 4 * (lane >> 4);
     if (!(lane & 7) && k <= j) {
-        double *o = (double *)(part + (size_t)k * gridDim.x + blockIdx.x);
+        double *o = (double *)(part + ((size_t)k * nb + sg) * G + g);
         o[(lane >> 3) & 1] = s;
     }
 }
@@ -708,6 +722,22 @@ int stream_grid(int Vc, int n2, int j) {
     return Vc < g ? Vc : g;
 }
 
+// The stream kernel, each right-hand side reading the blocks, or the matrix
+// cores, one read for all of them? The stream takes its time per right-hand
+// side, the matrix cores nearly the same for 2 as for 12. 12 steps, stream /
+// matrix cores: 2 right-hand sides, 4^3 x 8 coarse sites, N = 20: 373 / 578 us,
+// 8^3 x 16: 2.50 / 5.76 ms. They meet between 6 and 7 for three tiles of 16 rows
+// (N = 17 .. 24; 8^3 x 16, 6: 6.42 / 6.72 ms, 7: 7.48 / 7.01; 6^3 x 12, N = 24, 6:
+// 2.52 / 2.64, 7: 2.91 / 2.76), else between 3 and 4 (8^4, N = 12, 3: 1.26 / 1.41 ms, 4: 1.58 / 1.46; N = 30, 3.69 /
+// 3.84, 4.67 / 4.07) and, for the fewest and most vectors, 2 and 3 (N = 8, 2: 0.80
+// / 0.88, 3: 1.11 / 0.92; N = 32, 3.17 / 3.79, 4.34 / 3.99). Few sites leave the
+// chip idle and the number of kernels decides (2 per step and 4): 128 sites, N =
+// 20, 12 right-hand sides: 405 / 501 us; 256, N = 28, 6: 547 / 556, 7: 649 / 567.
+bool stream_rhs(int Vc, int n2, int nb) {
+    const int tiles = (n2 + 15) / 16, most = tiles == 3 ? 6 : n2 < 24 || n2 > 60 ? 2 : 3;
+    return nb <= most || (size_t)Vc * nb <= 1536;
+}
+
 }  // namespace
 
 size_t compact_arnoldi_scratch(const StencilOp &op, int m, int nb) {
@@ -731,6 +761,7 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
     const void *w = b;
     arnoldi_norm_kernel<<<grid, PTPB, 0, c->stream>>>((int)n, (const float2 *)b, part3);
 #define PASS(NV) arnoldi_pass_kernel<NV><<<grid, PTPB, 0, c->stream>>>(Vc, n2, op.nbr, vl, j + 1, part1, gs, y, t, part3, h1)
+    const bool stream = stream_rhs(Vc, n2, nb);
     int rc = MGDD_OK;
     for (int j = 0; j < m && !rc; j++) {
         Basis vl{};
@@ -743,11 +774,11 @@ int launch_compact_arnoldi(Ctx *c, const StencilOp &op, int m, int nb, const voi
         double2 *h2p = H2 + (size_t)(j ? j - 1 : 0) * (m + 1) * nb, *nrj = NR + (size_t)j * nb;
         const int gs = stream_grid(Vc, n2, j);
         int slot;
-        if (nb == 1) {
+        if (stream) {
             slot = kt_begin(c);
-            arnoldi_stream_kernel<<<gs, STPB, stream_lds(n2, j), c->stream>>>(
-                Vc, N, op.nbr, H, (const float2 *)w, part3, G, vl, j, vj, y, t, part1, h2p, nrj);
-            kt_end(c, slot, KF_COARSE, MGDD_F32, (double)Vc, abytes);
+            arnoldi_stream_kernel<<<gs * nb, STPB, stream_lds(n2, j), c->stream>>>(
+                Vc, N, nb, op.nbr, H, (const float2 *)w, part3, G, vl, j, vj, y, t, part1, h2p, nrj);
+            kt_end(c, slot, KF_COARSE, MGDD_F32, (double)Vc * nb, abytes);
         } else {
 #define VECTOR(NV)                                                                                                    \
     arnoldi_vector_kernel<NV><<<grid, PTPB, 0, c->stream>>>((int)n, vl, j, part3, G, (const float2 *)w, vj, h2p, nrj)

@@ -37,6 +37,8 @@ def coarse_rhs(lat, n, seed):
     ((4, 4, 4, 8), (2, 2, 2, 2), (4, 4, 4, 4), 20, 12),        # 32 coarse sites
     ((4, 8, 8, 8), (4, 2, 2, 4), (2, 2, 4, 4), 17, 15),        # 2048
     ((6, 6, 6, 12), (4, 4, 4, 4), (3, 4, 4, 4), 28, 12),       # 3456
+    ((4, 8, 8, 8), (4, 2, 2, 4), (2, 2, 4, 4), 8, 6),
+    ((4, 8, 8, 8), (4, 2, 2, 4), (2, 2, 4, 4), 31, 6),
 ])
 def test_alone_and_among_others(small, reps, agg, N, iters):
     lat = tiled_lattice(small, reps, (4, 4, 4, 4), agg, N, 71)
