@@ -312,11 +312,12 @@ __global__ __launch_bounds__(TPB) void restrict_kernel(int V, int Va, int N, con
     }
 }
 
+// xcd: neighbouring sites on one XCD, else in the order of the launch
 template <typename T, typename SP, typename SF, int R>
 __global__ __launch_bounds__(TPB) void prolong_kernel(int V, int Vc, int N, const int *__restrict__ site_agg,
                                                             const C<SP> *__restrict__ P, const C<T> *__restrict__ cin,
-                                                            C<SF> *__restrict__ f, int nrhs) {
-    const int wg = xcd_block(gridDim.x), chi = wg & 1, r0 = blockIdx.y * R;
+                                                            C<SF> *__restrict__ f, int nrhs, int xcd) {
+    const int wg = xcd ? xcd_block(gridDim.x) : (int)blockIdx.x, chi = wg & 1, r0 = blockIdx.y * R;
     const int i = (wg >> 1) * TPB + (int)threadIdx.x, d = i < V ? i : V - 1;
     const int a = site_agg[d], au = __builtin_amdgcn_readfirstlane(a);
     const size_t fs = (size_t)12 * V, xs = (size_t)Vc * 2 * N;
@@ -358,6 +359,33 @@ __global__ __launch_bounds__(TPB) void prolong_kernel(int V, int Vc, int N, cons
 #pragma unroll
         for (int c = 0; c < 6; c++) fr[(size_t)c * V] = mk<SF>((SF)acc[r][c].x, (SF)acc[r][c].y);
     }
+}
+
+// The same with one thread per (site, field) and both chiralities in it, the
+// fields of a site in consecutive threads: 12 values of P in flight. The same
+// sums, so the same bits.
+template <typename T>
+__global__ __launch_bounds__(TPB) void prolong_site_kernel(int V, int Vc, int N, const int *__restrict__ site_agg,
+                                                           const C<T> *__restrict__ P, const C<T> *__restrict__ cin,
+                                                           C<T> *__restrict__ f, int nrhs) {
+    const size_t i = (size_t)blockIdx.x * TPB + threadIdx.x;
+    if (i >= (size_t)V * nrhs) return;
+    const int r = (int)(i % nrhs), d = (int)(i / nrhs);
+    const int a = site_agg[d];
+    const size_t fs = (size_t)12 * V;
+    const C<T> *x = cin + ((size_t)r * Vc + a) * 2 * N;
+    C<T> acc[12];
+#pragma unroll
+    for (int c = 0; c < 12; c++) acc[c] = mk<T>(0, 0);
+    for (int k = 0; k < N; k++) {
+        const C<T> *pk = P + (size_t)k * fs;
+        const C<T> x0 = x[k], x1 = x[N + k];
+#pragma unroll
+        for (int c = 0; c < 12; c++) cfma(acc[c], pk[(size_t)c * V + d], c < 6 ? x0 : x1);
+    }
+    C<T> *fr = f + (size_t)r * fs;
+#pragma unroll
+    for (int c = 0; c < 12; c++) fr[(size_t)c * V + d] = acc[c];
 }
 
 // ---------------------------------------------------------------- coarse stencil y = D_c x
@@ -697,15 +725,47 @@ int launch_restrict(Ctx *c, int prec, int nrhs, const void *fine, void *coarse) 
     return hip_check(c, hipGetLastError(), "restrict kernel");
 }
 
+// One field in FP32 or FP64 and two in FP64 are served better by a thread per
+// site and field on lattices whose P comes from memory: FP64, N = 20, 16^3 x 32, 1
+// and 2 fields: 87 and 101 us against 96 and 111; 24^3 x 48, N = 28, 6^2 x 4^2 sites
+// an aggregate: 677 and 703 against 692 and 748; FP32, 1 field: 347 against 353.
+// Not so below 131072 sites (16^4: 43.9 and 60 against 39.2 and 42; FP32 20.5
+// against 19.3), nor one field on 2^20 sites or more (32^3 x 64, N = 20: 1740
+// against 1617, FP32 850 against 822).
+static bool prolong_by_site(const Ctx *c, int prec, int nrhs) {
+    if (c->g.V < 131072 || prec == MGDD_F16) return false;
+    return nrhs == 1 ? c->g.V < 1 << 20 : nrhs == 2 && prec == MGDD_F64;
+}
+
 int launch_prolong(Ctx *c, int prec, int nrhs, const void *coarse, void *fine) {
     const Level1 &L1 = c->c;
     const void *P = prec == MGDD_F64 ? L1.P64 : prec == MGDD_F32 ? L1.P32 : L1.P16;
-    const int R = rhs_per_thread(prec, nrhs);
-    const dim3 grid(2u * (unsigned)((c->g.V + TPB - 1) / TPB), (unsigned)((nrhs + R - 1) / R));
+    const unsigned nwg = (unsigned)((c->g.V + TPB - 1) / TPB);
+    // A P that fits the Infinity Cache (256 MB) is read from it the faster with an
+    // XCD's sites together (16^3 x 32, N = 20, FP32, 1 right-hand side: 38 us, in the
+    // order of the launch 41.6), one from memory with all XCDs' streams together
+    // (24^3 x 48, N = 24, FP32, 2: 326 against 342 us).
+    const bool cached = (size_t)12 * c->g.V * L1.N * csize(prec) <= 256000000;
+    if (prolong_by_site(c, prec, nrhs)) {
+        const unsigned n = (unsigned)(((size_t)c->g.V * nrhs + TPB - 1) / TPB);
+        if (prec == MGDD_F64)
+            prolong_site_kernel<double><<<n, TPB, 0, c->stream>>>(c->g.V, L1.Vc, L1.N, L1.site_agg, (const double2 *)P,
+                                                                  (const double2 *)coarse, (double2 *)fine, nrhs);
+        else
+            prolong_site_kernel<float><<<n, TPB, 0, c->stream>>>(c->g.V, L1.Vc, L1.N, L1.site_agg, (const float2 *)P,
+                                                                 (const float2 *)coarse, (float2 *)fine, nrhs);
+        return hip_check(c, hipGetLastError(), "prolong kernel");
+    }
+    // few sites: smaller groups, so that every CU has a workgroup (8^4, 12
+    // right-hand sides, FP32: 6.8 us, with all in one thread 11.2; 8^3 x 16 11.0 and
+    // 21.7; 16^2 x 8^2 14.6 and 23.6)
+    int R = rhs_per_thread(prec, nrhs);
+    while (R > 1 && 2 * nwg * ((nrhs + R - 1) / R) < 256) R = R > 8 ? 8 : R > 2 ? R - 2 : 1;
+    const dim3 grid(2 * nwg, (unsigned)((nrhs + R - 1) / R));
 #define PROLONG(T, SP, SF, RR)                                                                               \
     prolong_kernel<T, SP, SF, RR><<<grid, TPB, 0, c->stream>>>(c->g.V, L1.Vc, L1.N, L1.site_agg,             \
                                                                (const C<SP> *)P, (const C<T> *)coarse,       \
-                                                               (C<SF> *)fine, nrhs)
+                                                               (C<SF> *)fine, nrhs, cached)
     MULTI(PROLONG);
 #undef PROLONG
     return hip_check(c, hipGetLastError(), "prolong kernel");
