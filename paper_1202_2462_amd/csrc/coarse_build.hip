@@ -69,7 +69,9 @@ __device__ inline void forward_hop(const double2 *lk, size_t stride, const v2d *
 }
 
 // One workgroup per (aggregate a, term t): t = 0 the self term X over all
-// sites of a, t = 1 + mu the forward hop over the sites of its + mu face.
+// sites of a, or each of `parts` workgroups over `per` of them, t = 1 + mu the
+// forward hop over the sites of its + mu face. The parts' sums are kept where
+// the backward blocks of a belong and added up by dc_parts_kernel.
 // Sixteen sites of the list a step, four of them per wave, and the block's
 // columns j = (chi', k') in NT tiles of 16 one after the other. Lane (jj, s) =
 // (lane % 16, lane / 16) forms D P_j at its wave's site s, all 12 components in
@@ -89,22 +91,28 @@ __device__ inline void forward_hop(const double2 *lk, size_t stride, const v2d *
 // they take from L2 (67 GB against 37 past it), 9.4 ms; one workgroup per
 // column with the dot products on the vector units and sums through LDS 29.4 ms.
 // Eight sites a step with a wave per tile and half of them, two waves on some
-// SIMDs and one on others: 8.5 ms; the same with three waves a SIMD spills.
+// SIMDs and one on others: 8.5 ms; the same with three waves a SIMD spills. Four
+// tiles (N >= 25) spill too, 240 B a lane: P and D_c together of 24^3 x 48, 4^4
+// sites, N = 24: 10.9 ms, 25: 15.2, 28: 15.9, 32: 17.6 (one column a workgroup: 38,
+// 42, 51, 65).
+
 // LDS place of (component, test vector, site of the step): the sites are
 // permuted by the vector, so that the 16 vectors of an A operand lie in all banks
 __device__ inline int pk_at(int N, int c, int k, int s) { return (c * N + k) * STEP + (s ^ (k & 15)); }
 
 template <int NT, int RT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(1))) void dc_forward_kernel(
-    Geom g, AggGeom ag, int N, int Va, const int *__restrict__ agg_sites, const int *__restrict__ face_sites,
+    Geom g, AggGeom ag, int N, int Va, int parts, int per, const int *__restrict__ agg_sites,
+    const int *__restrict__ face_sites,
     const double2 *__restrict__ Up, const double2 *__restrict__ Ap, const double2 *__restrict__ P, double2 *__restrict__ Dc) {
     extern __shared__ double2 pk[];   // [12 N + 72][STEP]: P, links, clover term; at the end [WAVES][sums of a tile]
     constexpr int ROWS = 64 * WAVES / STEP, PER = (96 * NT + ROWS - 1) / ROWS, PERU = (72 + ROWS - 1) / ROWS;
-    const int wg = xcd_block(gridDim.x), a = wg / 5, t = wg % 5;
+    const int wg = xcd_block(gridDim.x), a = wg / (4 + parts), part = wg % (4 + parts);
+    const int t = part < parts ? 0 : part - parts + 1;
     const int n2 = 2 * N, lane = threadIdx.x & 63, s = lane >> 4, wave = threadIdx.x >> 6;
     const size_t V = g.V;
-    const int *list = agg_sites + (size_t)a * Va;
-    int count = Va;
+    const int *list = agg_sites + (size_t)a * Va + (t ? 0 : part * per);
+    int count = per < Va - part * per ? per : Va - part * per;
     if (t) {
         size_t o = 0;
 #pragma unroll
@@ -315,7 +323,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(1)))
     }
     // the waves' sums of a tile: [wave][h][rt][v][lane]; a wave adds up and stores
     // its share of the rows
-    double2 *res = Dc + ((size_t)a * 9 + (t ? 2 * t - 1 : 0)) * n2 * n2;
+    double2 *res = Dc + ((size_t)a * 9 + (t ? 2 * t - 1 : 2 * part)) * n2 * n2;
     constexpr int SUMS = 2 * RT * 4;
 #pragma unroll
     for (int tl = 0; tl < NT; tl++) {
@@ -471,6 +479,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             }
 }
 
+// the self terms' parts added up in order: block 0 of an aggregate += blocks 2, 4, 6
+__global__ __launch_bounds__(256) void dc_parts_kernel(int blk, int parts, double2 *__restrict__ Dc) {
+    double2 *B = Dc + (size_t)blockIdx.x * 9 * blk;
+    const int e = blockIdx.y * 256 + threadIdx.x;
+    if (e >= blk) return;
+    double2 v = B[e];
+    for (int p = 1; p < parts; p++) v = cadd(v, B[(size_t)2 * p * blk + e]);
+    B[e] = v;
+}
+
 // The other half of D_c from the forward one, and the FP32 copies: all 9
 // blocks, and the compact [Vc][5] (self block and forward hops). One workgroup
 // per (a, direction): the self block X + s X^H s in place (every thread holds
@@ -519,18 +537,19 @@ int launch_coarse_build(Ctx *c) {
     AggGeom ag{};
     for (int m = 0; m < 4; m++) ag.a[m] = L1.agg[m];
     const int tiles = (2 * L1.N + 15) / 16;
-    const unsigned nwg = 5u * (unsigned)L1.Vc;
+    const DcSplit split = dc_split(L1.Va, L1.Vc, STEP);
     const size_t stage = (size_t)(12 * L1.N + 72) * STEP * 16, sums = (size_t)WAVES * 2 * (tiles > 2 ? 2 : 1) * 4 * 64 * 16;
     const size_t lds = stage > sums ? stage : sums;
+    const bool small = L1.Va < 64 || lds > c->lds_max;
 #define FORWARD(NT, RT)                                                                                     \
-    dc_forward_kernel<NT, RT><<<nwg, 64 * WAVES, lds, c->stream>>>(g, ag, L1.N, L1.Va, L1.agg_sites, L1.face_sites, \
-                                                                   (const double2 *)c->U64, (const double2 *)c->A64, \
-                                                                   (const double2 *)L1.P64, (double2 *)L1.Dc64)
+    dc_forward_kernel<NT, RT><<<(4 + split.parts) * L1.Vc, 64 * WAVES, lds, c->stream>>>(                            \
+        g, ag, L1.N, L1.Va, split.parts, split.per, L1.agg_sites, L1.face_sites, (const double2 *)c->U64,               \
+        (const double2 *)c->A64, (const double2 *)L1.P64, (double2 *)L1.Dc64)
 #define SMALL(RT)                                                                                            \
-    dc_forward_small_kernel<RT><<<nwg, 64u * (unsigned)tiles, 0, c->stream>>>(                               \
+    dc_forward_small_kernel<RT><<<5 * L1.Vc, 64u * (unsigned)tiles, 0, c->stream>>>(                               \
         g, ag, L1.N, L1.Va, L1.agg_sites, L1.face_sites, (const double2 *)c->U64, (const double2 *)c->A64,   \
         (const double2 *)L1.P64, (double2 *)L1.Dc64)
-    if (L1.Va < 64 || lds > c->lds_max) {
+    if (small) {
         if (tiles <= 2) SMALL(1); else SMALL(2);
     } else if (tiles == 1) {
         FORWARD(1, 1);
@@ -545,6 +564,12 @@ int launch_coarse_build(Ctx *c) {
 #undef FORWARD
     int rc = hip_check(c, hipGetLastError(), "D_c forward kernel");
     if (rc) return rc;
+    if (!small && split.parts > 1) {
+        const int blk = 4 * L1.N * L1.N;
+        dc_parts_kernel<<<dim3(L1.Vc, (blk + 255) / 256), 256, 0, c->stream>>>(blk, split.parts, (double2 *)L1.Dc64);
+        rc = hip_check(c, hipGetLastError(), "D_c parts kernel");
+        if (rc) return rc;
+    }
     dc_finish_kernel<<<dim3((unsigned)L1.Vc, 9), FIN_TPB, 0, c->stream>>>(L1.N, L1.cnbr, (double2 *)L1.Dc64,
                                                                         (float2 *)L1.Dc32, (float2 *)L1.Dh32);
     return hip_check(c, hipGetLastError(), "D_c finish kernel");

@@ -64,6 +64,22 @@ inline RestrictSplit restrict_split(int N, size_t workgroups) {
 }
 int launch_prolong(Ctx *c, int prec, int nrhs, const void *coarse, void *fine);
 int launch_coarse_build(Ctx *c);
+
+// How the D_c build divides the Va sites of an aggregate's self term: `parts`
+// (at most 4) workgroups of `per` sites, the last with what is left, none with
+// nothing; per is a multiple of the kernel's step. Up to 512 aggregates the
+// self terms, four times as long as the hops on 4^4 sites and with four hops a
+// site, would be what the launch waits for. P and D_c together, one part / four: 16
+// aggregates (8^4), N = 8: 176 / 104 us, N = 20: 468 / 235; 512 (16^3 x 32), N =
+// 8: 662 / 573, N = 20: 2.18 / 1.99 ms. More fill the chip either way: 24^3 x 48,
+// 3x4x4x4 sites, N = 21: 13.45 / 13.68 ms.
+struct DcSplit {
+    int parts, per;
+};
+inline DcSplit dc_split(int Va, int Vc, int step) {
+    const int steps = (Va + step - 1) / step, most = Vc <= 512 ? 4 : 1, per = (steps + most - 1) / most;
+    return {(steps + per - 1) / per, per * step};
+}
 int launch_coarse_apply(Ctx *c, int prec, int nrhs, const void *in, void *out);
 
 // Fused Arnoldi process on D_c for the coarse GMRES (arnoldi.hip); m <= 15.
