@@ -179,7 +179,9 @@ int mgdd_dirac_apply(mgdd_ctx *ctx, int prec, int nrhs, const void *in, void *ou
  * shifted block inverses B_j(lambda) of the second setup part use shift =
  * lambda). prec MGDD_F16: b and z in half precision, the sweep in FP32 (z
  * rounded once per colour step when it is stored); needs special unitary
- * links, else MGDD_EINVAL. Asynchronous. */
+ * links, else MGDD_EINVAL. MGDD_F64 reads links as two rows where the third is
+ * conj(row 0 x row 1) to 8 ulp of 1, MGDD_F32 and MGDD_F16 where it is to 1e-12,
+ * and rebuilds that row. Asynchronous. */
 int mgdd_sap(mgdd_ctx *ctx, int prec, int nrhs, const int block[4], int nsweeps, int mr_iters, double shift_re,
              double shift_im, const void *b, void *z);
 

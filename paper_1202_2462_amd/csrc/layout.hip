@@ -70,11 +70,14 @@ __global__ void links_kernel(Geom g, const double2 *__restrict__ Uc, double2 *__
             U32[((size_t)mu * 9 + k) * g.V + d] = make_float2((float)u.x, (float)u.y);
         }
         // a special unitary link has row 2 = conj(row 0 x row 1): the stencil
-        // kernels then read rows 0 and 1 only (flag 4 when some link is not)
+        // kernels then read rows 0 and 1 only (flag 4 when some link is not; flag
+        // 16 when one is further from it than the rounding of its entries makes,
+        // 8 ulp of 1: the FP64 sweeps then read all rows)
         for (int a = 0; a < 3; a++) {
             const int b = (a + 1) % 3, c = (a + 2) % 3;
             const double2 x = csub(cmul(r[b], r[3 + c]), cmul(r[c], r[3 + b]));
-            if (fabs(x.x - r[6 + a].x) > 1e-12 || fabs(-x.y - r[6 + a].y) > 1e-12) atomicOr(bad, 4);
+            const double off = fmax(fabs(x.x - r[6 + a].x), fabs(-x.y - r[6 + a].y));
+            if (!(off <= 8 * 0x1p-52)) atomicOr(bad, off <= 1e-12 ? 16 : 4 | 16);
         }
     }
 }
@@ -531,6 +534,7 @@ int launch_gauge_ingest(Ctx *c, const double2 *Ucanon) {
         if (rc) return rc;
     }
     c->links_su3 = !(hbad & 4);
+    c->links_exact = !(hbad & 16);
     if (hbad & 2) return fail(c, MGDD_ENAN, "gauge field holds NaN or Inf");
     if (hbad & 1) return fail(c, MGDD_EINVAL, "clover term is singular on some site");
     return MGDD_OK;

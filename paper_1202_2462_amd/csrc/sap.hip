@@ -923,8 +923,10 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
                       sap_site_lds(g.Vb) <= c->lds_max;
     // FP64: the two-lane kernel where its LDS fits (12 x 20 x 16 x 24 with 2^2
     // x 4^2 blocks, 3 right-hand sides, one colour: 101 us against 158 with
-    // one lane per site and the links read from memory in every MR step)
-    const bool two64 = prec == MGDD_F64 && c->links_su3 && 2 * ldsc <= c->lds_max;
+    // one lane per site and the links read from memory in every MR step), for
+    // links whose rebuilt row is theirs up to rounding: others are special
+    // unitary to 1e-12 only, and so would the sweep be right
+    const bool two64 = prec == MGDD_F64 && c->links_exact && 2 * ldsc <= c->lds_max;
     const bool shifted = sre != 0 || sim != 0;
     const int slot = kt_begin(c);
     int rc = MGDD_OK;
