@@ -118,8 +118,9 @@ int mgdd_set_allocator(mgdd_ctx *ctx, mgdd_alloc_fn alloc, mgdd_free_fn free_fn,
  * site beyond the summation order of the FP32 Schwarz kernels):
  *   sap_lanes: lanes per site of the FP32 Schwarz colour kernel (Algorithm
  *     2.1): 0 automatic (special unitary links whose staged rows fit in
- *     LDS: 2, or one lane with those rows staged on lattices of 262144
- *     sites or more; else 4 when the staged links fit, else 1),
+ *     LDS: 2, or on large lattices (262144 sites; 655360 or more, half
+ *     storage 1048576) one lane with those rows staged; else 4 when the
+ *     staged links fit, else 1),
  *     1 (one lane per site, spinors in LDS), 2 (two lanes per site, one per
  *     chirality, rows 0 and 1 of the block's links staged in LDS; needs
  *     special unitary links) or 4 (four lanes per site, the whole links

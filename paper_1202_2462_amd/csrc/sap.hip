@@ -912,14 +912,22 @@ int launch_sap_colour(Ctx *c, int prec, int nrhs, int col, int mr, double sre, d
                                  "link rows in LDS"
                                : "the four-lanes-per-site Schwarz kernel needs the block's links in LDS");
     // Special unitary links in FP32 and half storage: one lane per site needs
-    // fewer instructions, two lanes give twice the waves. A colour of 131072
-    // sites is two waves of one-lane sites per SIMD, all that fit, and from
-    // there on one lane is faster (one sweep, 4 MR steps, FP32, one / two
-    // lanes: 16^3 x 32 73 / 64 us, 16^2 x 32^2 97 / 105, 24^3 x 48 258 / 276,
-    // 32^3 x 64 645 / 773; 4^3 x 2 and 2^2 x 4^2 blocks cross at the same
-    // size). The number of right-hand sides does not enter: one of them gets
+    // fewer instructions, two lanes give twice the waves. The one-lane kernel's
+    // two waves per SIMD hold 131072 sites, so that 262144 sites (two colours) fill
+    // the chip once: one full round, or many, the last of which may be short.
+    // One sweep, 1 right-hand side, 4 MR steps, two lanes / one: FP32, 4^4 blocks
+    // 16^2 x 32^2 (1 round) 103 / 94 us, 24^4 (1.3) 149 / 151, 24^2 x 32^2 (2.3)
+    // 231 / 230, 24^3 x 48 (2.5) 277 / 256, 32^3 x 64 (8) 763 / 646; 4^3 x 2 106 / 95, 146
+    // / 155, 211 / 221, 253 / 247, 755 / 642. Half storage gains less: 24^3 x 48
+    // 250 / 244 and 231 / 241 (2 steps: 186 / 193 and 174 / 191), 32^4 (4) 354 / 324
+    // and 351 / 339. The number of right-hand sides does not enter: one of them gets
     // the same result alone and among others.
-    const bool site = prec != MGDD_F64 && c->sap_lanes == 0 && lanes == 2 && g.V >= 262144 &&
+    // The fewer MR steps, the more the kernels' common memory phases count: with
+    // up to 2 of them blocks of fewer sites need more rounds (24^3 x 48, 4^3 x 2,
+    // FP32 199 / 204; 32^4, half storage 266 / 270).
+    const int round = 262144, need = (prec == MGDD_F32 ? 5 : 8) + (mr <= 2 && g.Vb < 256 ? 3 : 0);   // halves of a round
+    const bool full = g.V == round && (prec == MGDD_F32 || g.Vb != 128);   // half storage, 4^3 x 2, 3 fields: 254 / 266
+    const bool site = prec != MGDD_F64 && c->sap_lanes == 0 && lanes == 2 && (full || 2LL * g.V >= (long long)need * round) &&
                       sap_site_lds(g.Vb) <= c->lds_max;
     // FP64: the two-lane kernel where its LDS fits (12 x 20 x 16 x 24 with 2^2
     // x 4^2 blocks, 3 right-hand sides, one colour: 101 us against 158 with
