@@ -77,14 +77,18 @@ def sap_flops_per_site(k):
     return (1 + k) * 1896 + k * 336
 
 
-# HBM traffic of the Schwarz kernel from hardware counters at this workload,
-# and the sources it was taken from (the figure is dropped when they changed)
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sapc_kernel_f32_48x48x48x96_hbm_traffic.md")
-SAP_SOURCES = ["paper_1202_2462_amd/csrc/sap.hip", "paper_1202_2462_amd/csrc/stencil.h",
-               "paper_1202_2462_amd/csrc/mgdd_internal.h", "paper_1202_2462_amd/csrc/geometry.h"]
-COARSE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "arnoldi_apply_f32_48x48x48x96_hbm_traffic.md")
-COARSE_SOURCES = ["paper_1202_2462_amd/csrc/arnoldi.hip", "paper_1202_2462_amd/csrc/coarse.h",
-                  "paper_1202_2462_amd/csrc/mgdd_internal.h", "paper_1202_2462_amd/csrc/transfer.h"]
+# HBM traffic from hardware counters at this workload of the kernels that the
+# rooflines name, and the sources that decide what they read: the kernel's file,
+# that of the rule which chooses it, and what they include (the figure is
+# dropped when these changed)
+CSRC = "paper_1202_2462_amd/csrc/"
+SAP_KERNEL, COARSE_KERNEL = "sap_site_kernel", "arnoldi_stream_kernel"
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sap_site_f32_48x48x48x96_hbm_traffic.md")
+SAP_SOURCES = [CSRC + f for f in ("sap_site.hip", "sap.hip", "schwarz.h", "lanes.h", "stencil.h", "mgdd_internal.h",
+                                  "geometry.h")]
+COARSE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "arnoldi_stream_f32_48x48x48x96_hbm_traffic.md")
+COARSE_SOURCES = [CSRC + f for f in ("arnoldi_compact.hip", "lanes.h", "stencil.h", "transfer.h", "mgdd_internal.h",
+                                     "geometry.h")]
 
 
 def sources_digest(files):
@@ -553,7 +557,7 @@ def main():
         achieved = bytes_launch / t_launch / 1e9
         tps = counter_traffic(TRAFFIC_FILE, SAP_SOURCES) if big else None
         lines["sap"] = (sap_ms, {
-            "bound": "hbm", "kernel": "sap_site_kernel<256, float> (FP32 Schwarz colour step, 4 MR steps)",
+            "bound": "hbm", "kernel": SAP_KERNEL + "<256, float> (FP32 Schwarz colour step, 4 MR steps)",
             "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
             "traffic": None if tps is None else tps * units_launch,
             "launches": sap_n, "us_per_launch": t_launch * 1e6, "total_ms_in_timed_steps": sap_ms,
@@ -570,7 +574,7 @@ def main():
         tpc = counter_traffic(COARSE_TRAFFIC_FILE, COARSE_SOURCES) if big else None
         n2 = 2 * bench.N
         lines["coarse"] = (c_ms, {
-            "bound": "hbm", "kernel": "arnoldi_stream_kernel (coarse GMRES step on the compact FP32 D_c: self block "
+            "bound": "hbm", "kernel": COARSE_KERNEL + " (coarse GMRES step on the compact FP32 D_c: self block "
                                       "and forward hops stored and read once, backward hops from "
                                       "gamma5^c-hermiticity)",
             "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
