@@ -328,7 +328,7 @@ __global__ __launch_bounds__(STPB) __attribute__((amdgpu_waves_per_eu(3))) void 
 // t_mu. Operand layouts as in the coarse apply: A [i][k] in lane i + 16 k,
 // B[k][j] in lane j + 16 k, result register v of lane l holds row 4 (l / 16) +
 // v of column l % 16. One MFMA is one batch of the stream kernel's sums.
-// Bound: the latency of each block's way through LDS (matrix cores 34 %, vector
+// Bound: the latency of each block's way through LDS (matrix cores 26 %, vector
 // units 28 % busy). 6^3 x 12 coarse sites, N = 24, 12 right-hand sides: 161 us,
 // and 46 to 181 us the other three kernels; reading the blocks once per
 // right-hand side took 725 us and two passes of 92 us.

@@ -206,7 +206,7 @@ template <typename T, typename S, bool RECON, int R> struct BlockHops {
 // hold as much in LDS as the 4 MB of L2, so that most of a block's halo comes
 // from beyond it (24^3 x 48, FP32, 12 right-hand sides: 4.0 GB read of the
 // 1.1 GB that are there once). Before (R = 1) and after, 24^3 x 48: FP32 12
-// right-hand sides 1135 -> 862 us, half storage 861 -> 588, FP64 4 621 -> 520.
+// right-hand sides 1106 -> 839 us, half storage 861 -> 588, FP64 4 621 -> 520.
 // Not faster: the groups of one range of sites one after the other instead of
 // together, links or clover term with the non-temporal policy (2 - 10 % slower).
 template <typename T, typename S, typename O, bool RECON, int R, int WAVES>
@@ -302,8 +302,9 @@ template <typename T, int MU, bool FWD> __device__ inline void quad_lower(const 
 // in flight at once; the sum then goes from lane to lane in the order of
 // dirac_kernel's, so that both give the same bits. A lane finishes three
 // components of the result. Bound: the latency of one chain of loads, where
-// dirac_kernel has eight (and 16 of 256 CUs at work on 8^4 sites): 8^4, FP64, 6.0 us
-// against 10.3.
+// dirac_kernel has eight (and 16 of 256 CUs at work on 8^4 sites): 8^4, FP64, pass
+// after pass 5.3 us against 11.6, the first on a new field after 2 GB of other
+// traffic, waited for, 18.0 against 28.2.
 constexpr int QSITES = 16;   // sites of a workgroup, one wave
 template <typename T, typename S, typename O, bool RECON>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) void dirac_quad_kernel(

@@ -11,9 +11,10 @@
 // block's sites), so that every lane runs the same instructions; in the residual
 // it is read from memory, the arithmetic being shared.
 //
-// Bound: issue of vector instructions. A colour step of 32^3 x 64 (1 048 576
-// sites, 4 MR steps, FP32): 348 us; with two lanes per site, which exchange
-// half of each hop sum and select by chirality, 385 us.
+// Bound: issue of vector instructions (48^3 x 96: busy for 76 %; 1245 B per site
+// update between L2 and memory of 768 that are there once). One sweep of 32^3 x
+// 64, 4 MR steps, FP32: 646 us; with two lanes per site, which exchange half of
+// each hop sum and select by chirality, 763 us.
 #include "lanes.h"
 #include "schwarz.h"
 #include "stencil.h"

@@ -1,9 +1,7 @@
 // Aggregation interpolation (Section 3): P from test vectors by a local
-// orthonormalisation per (aggregate, chirality), restriction P^H,
-// prolongation P, and the coarse operator D_c = P^H D P built column by
-// column from the terms of D (self term plus the hops that cross each face of
-// an aggregate) followed by a restriction. The coarse stencil apply lives here
-// as well.
+// orthonormalisation per (aggregate, chirality), restriction P^H and
+// prolongation P, the tables of the coarse level, and the coarse stencil apply.
+// The coarse operator D_c = P^H D P is built in coarse_build.hip.
 #include "lanes.h"
 #include "stencil.h"
 #include "transfer.h"
@@ -498,9 +496,10 @@ __global__ __launch_bounds__(64) void coarse_apply_mfma_kernel(int Vc, int N, in
 // from this many right-hand sides on, D_c is applied on the matrix cores
 static int MFMA_MIN_RHS = 4;
 
-// Order in which the coarse GMRES step visits the coarse sites. A site reads
-// the forward blocks of its four backward neighbours again (the compact FP32
-// D_c), so these should still be in the L2 of its XCD, and the XCDs take
+// Order in which arnoldi_apply_kernel visits the coarse sites: the coarse GMRES
+// step in FP64, and in FP32 where the workspace has no room for the compact
+// steps. In FP32 a site reads the forward blocks of its four backward neighbours
+// again, so these should still be in the L2 of its XCD, and the XCDs take
 // contiguous eighths of the order. Lexicographic order leaves the z and t
 // neighbours far behind; here the sites go in 4-D tiles, time fastest within
 // a tile, the tiles in lexicographic order. The spatial extents of a tile are
