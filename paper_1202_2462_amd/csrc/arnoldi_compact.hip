@@ -524,8 +524,9 @@ __global__ __launch_bounds__(PTPB) void arnoldi_vector_kernel(int n, Basis V, in
 // that both give the same bits. A lane holds Q pairs of a site's 5 n2 entries
 // (128 (Q - 1) < 5 n2 <= 128 Q) for K basis vectors, the next site's in flight.
 // part: [k][segment][workgroup]. Grid (G, nb, ceil((j + 1) / 4 K)), G as the
-// stream kernel's. Bound: the basis, read at a site and its four forward
-// neighbours, from L2. 12 right-hand sides, steps 1 to 12, 6^3 x 12 coarse sites,
+// stream kernel's. Bound: vector instructions (busy for 68 %: every entry of the
+// basis is widened and used five times, at its site and from its four backward
+// neighbours). 12 right-hand sides, steps 1 to 12, 6^3 x 12 coarse sites,
 // N = 24: 16 to 83 us (K = 1: 15 to 85, 4: 20 to 75), 8^3 x 16, N = 20: 39 to
 // 269. Sums of <v_k, yf + sum t>, which read the basis once but in another order,
 // took 13 to 39 and 31 to 98 us.
