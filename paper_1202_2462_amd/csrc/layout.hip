@@ -56,13 +56,14 @@ __global__ void links_kernel(Geom g, const double2 *__restrict__ Uc, double2 *__
     int X[4];
     site_coords(g, d, X);
     int s = X[0] + g.L[0] * (X[1] + g.L[1] * (X[2] + g.L[2] * X[3]));
+    int flags = 0;
     for (int mu = 0; mu < 4; mu++) {
         // antiperiodic in t: the hop across the time boundary carries a sign
         double sg = (antiperiodic && mu == 3 && X[3] == g.L[3] - 1) ? -1.0 : 1.0;
         double2 r[9];
         for (int k = 0; k < 9; k++) {
             double2 u = Uc[((size_t)s * 4 + mu) * 9 + k];
-            if (!isfinite(u.x) || !isfinite(u.y)) atomicOr(bad, 2);
+            if (!isfinite(u.x) || !isfinite(u.y)) flags |= 2;
             r[k] = u;
             u.x *= sg;
             u.y *= sg;
@@ -77,9 +78,11 @@ __global__ void links_kernel(Geom g, const double2 *__restrict__ Uc, double2 *__
             const int b = (a + 1) % 3, c = (a + 2) % 3;
             const double2 x = csub(cmul(r[b], r[3 + c]), cmul(r[c], r[3 + b]));
             const double off = fmax(fabs(x.x - r[6 + a].x), fabs(-x.y - r[6 + a].y));
-            if (!(off <= 8 * 0x1p-52)) atomicOr(bad, off <= 1e-12 ? 16 : 4 | 16);
+            if (!(off <= 8 * 0x1p-52)) flags |= off <= 1e-12 ? 16 : 4 | 16;
         }
     }
+    // a field may have them on every site: one atomic per thread until they are there
+    if (flags & ~*(const volatile int *)bad) atomicOr(bad, flags);
 }
 
 struct M3 { double2 m[9]; };
